@@ -53,6 +53,17 @@ __host__ __device__ inline void tile_coords(int32_t t, const Sched &s,
 // below n_tiles.  tile_id(tm, tn) = tm * tiles_n + tn is the sub-tensor id
 // used by tile_partition_check.
 
+// Simple kernel: block of sub-tensors that program p of n_prog owns.  Blocks
+// are numbered down the block columns (blocks_m per column), so that the
+// programs of one XCD share columns of B.
+__host__ __device__ inline void simple_block(int32_t p, int32_t n_prog,
+                                             int32_t blocks_m, int32_t &bm,
+                                             int32_t &bn) {
+    const int32_t t = program_slot(p, n_prog);
+    bm = t % blocks_m;
+    bn = t / blocks_m;
+}
+
 // Kernel arguments of one tiled product.
 struct GemmArgs {
     const void *a;
@@ -144,7 +155,10 @@ struct SimpleArgs {
     int64_t lda, ldb, ldc;
     int32_t M, N, K;
     int32_t a_dtype, b_dtype, c_bf16, b_nk;
-    int32_t bm, bn;
+    int32_t bm, bn;      // sub-tensor
+    int32_t gm, gn;      // sub-tensors per program: gm bm and gn bn <= 128
+    int32_t blocks_m;    // programs per block column
+    int32_t n_prog;
 };
 hipError_t launch_simple(const SimpleArgs &a, hipStream_t st);
 
