@@ -129,10 +129,14 @@ typedef enum tg_sched {
     TG_SCHED_PINGPONG = 2, /* two wavefront groups alternate between loading
                               and contracting, one phase apart; needs K a
                               multiple of 16 bytes of the operand type      */
-    TG_SCHED_CROSS = 3,    /* lock-step with the hand-over barrier of the
-                              next K tile placed before the last K step of
-                              the current one (bf16); the default for B
-                              stored N x K                                  */
+    TG_SCHED_CROSS = 3,    /* the next K tile handed over inside the current
+                              one.  Two stages (the default for 256 x 256
+                              sub-tensors of bf16 and e4m3): the phased
+                              schedule, four phases per K tile, two wavefront
+                              groups one slot apart, loads of half tiles five
+                              phases ahead.  More stages (bf16): lock-step
+                              with the hand-over barrier before the tile's
+                              last K step                                   */
     TG_SCHED_STAGED = 4,   /* four wavefronts of 128 x 128 outputs; each K
                               tile read from HBM into registers two tiles
                               ahead and stored into a two-stage LDS ring
@@ -144,11 +148,9 @@ typedef enum tg_sched {
                               in one burst a tile period ahead, freeing its
                               stage for loads NS - 1 tiles ahead (bf16, B
                               stored N x K, K a multiple of 32)             */
-    TG_SCHED_CROSS_WARM = 6 /* the cross-tile schedule (two stages, B stored
-                              N x K, bf16) touching the L2 lines of the K
-                              tile two tiles beyond the one being loaded,
-                              so that its direct loads hit the L2 where the
-                              operands stream from HBM (long K)             */
+    TG_SCHED_CROSS_WARM = 6 /* TG_SCHED_CROSS of two stages under the name
+                              that the long-K default (bf16, B stored N x K)
+                              and tuning files of long products use        */
 } tg_sched;
 
 typedef struct tg_config {
@@ -525,7 +527,7 @@ tg_status tile_tune_cache_load(const char *path);
  * the sub-tensors per program; the fraction of the last round of
  * sub-tensors that has work; the useful fraction of the padded output
  * area; a flag for the ping-pong schedule; 1 for the cross-tile schedule,
- * 2 for the cross-tile schedule with the L2 warm-up, else 0; log2 splitk;
+ * 2 for TG_SCHED_CROSS_WARM, else 0; log2 splitk;
  * a flag for the configuration the fixed heuristic would pick.
  * tile_picker_set installs a cost model (host copy of the parameters in the
  * layout of tile_mlp_*, with per-feature mean and standard deviation used

@@ -67,6 +67,15 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
     return (uint16_t)(u >> 16);
 }
 
+// Two floats -> two bfloat16 (low half first) by the packed hardware
+// conversion: the same bits as f32_to_bf16_bits for all 2^32 patterns,
+// checked exhaustively (the compiler's own conversion of a pair).
+__device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi) {
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(
+        uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2_t));
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) {
     return __builtin_bit_cast(float, h << 16);
 }

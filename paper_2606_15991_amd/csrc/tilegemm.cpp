@@ -554,11 +554,9 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
         } else if (cfg.bm == 0 || cfg.bn == 0) {
             return fail(TG_E_ARG, "config bm/bn: set both or neither");
         }
-        // Long K (at least 16384 and twice the larger of M and N): the
-        // operands stream from HBM rather than the last-level cache, and the
-        // cross-tile schedule with the L2 warm-up is the faster one (measured
-        // +3.5 % at 8192 x 4096 x 16384, +9 % at 4096^2 x 32768, +59 % at
-        // 2048^2 x 65536; -5 % at 8192^3).
+        // Long K (at least 16384 and twice the larger of M and N) keeps its
+        // own schedule name, which plans and tuning files carry; the kernel
+        // is the phased one either way.
         if (cfg.sched == 0 && cfg.wm == 0 && cfg.wn == 0 && cfg.bk == 0 &&
             cfg.stages == 0 && L.gemm_dt == TG_BF16 && p.b_nk &&
             cfg.bm == 256 && cfg.bn == 256 && L.Kc >= 16384 &&
