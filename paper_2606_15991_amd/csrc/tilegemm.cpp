@@ -274,19 +274,54 @@ int find_variant(int dt, int bm, int bn, int wm, int wn, int bk, int stages,
 
 bool chunk_multiple(int64_t K, int dt) { return (K * esize(dt)) % 16 == 0; }
 
-// Default tile choice: the largest square tile that still gives every
-// compute unit close to one sub-tensor.
-int default_tile(int dt, int64_t M, int64_t N, int cus) {
-    const int sizes_lp[] = {256, 128, 64, 32};
-    const int sizes_f32[] = {128, 64, 32};
-    const int *sz = dt == TG_F32 ? sizes_f32 : sizes_lp;
-    int nsz = dt == TG_F32 ? 3 : 4;
+int64_t tiles_of(int64_t M, int64_t N, int s) {
+    return ((M + s - 1) / s) * ((N + s - 1) / s);
+}
+
+// Default sub-tensor of a tiled product, and LDS stages where they matter
+// (0: the variant table's first).  With t(s) sub-tensors of s x s on `cus`
+// compute units, measured in a graph of one launch each (B stored N x K):
+//  256 (phased) where 128 takes more than one program per compute unit and
+//      either t(256) reaches half of them or t(128) passes two: bf16 3072^3
+//      (t(256) = 144) 61 us against 97, 2048 x 5120 x 5120 (160) 96 against
+//      154; but 2816 x 2560 x 3000 (110) 63 against 59, 2048^3 42 against 27.
+//      Not for outputs of at most 128 rows or columns (64 x 65536 x 512: 19
+//      against 15 with 64);
+//  128: bf16, eight wavefronts and four stages, from eleven in twenty compute
+//      units on: 1536^3 (t(128) = 144) 19.6 us against 22.6 with 64, 512 x
+//      5120 x 5120 (160) 52.6 against 65, but 256 x 8192 x 4096 (128) 42.8
+//      against 39.7; two stages (two programs per compute unit) past one
+//      round: 2304^3 (324) 37.6 against 47 with 256.  e4m3, four wavefronts
+//      and two stages, from three in four on: 1536^3 (144) 12.0 against 11.0;
+//  64: four stages where all programs are then resident at once (two per
+//      compute unit) and there are at least 36 K tiles: bf16 128 x 5120 x
+//      5120 38 us against 54, 64 x 4096 x 4096 30.8 against 43; but bf16
+//      1536^3 (t(64) = 576) 31.5 against 22.6 and e4m3 200 x 300 x 4000 (31
+//      K tiles) 15.8 against 14.8;
+//  32 where 64 leaves a quarter of the compute units idle and K is shorter.
+// f32: the largest that gives three in four compute units a sub-tensor.
+struct DefaultTile {
+    int size, stages;
+};
+DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, int cus) {
     if (cus <= 0) cus = 256;
-    for (int i = 0; i < nsz; ++i) {
-        int64_t t = ((M + sz[i] - 1) / sz[i]) * ((N + sz[i] - 1) / sz[i]);
-        if (t * 4 >= (int64_t)cus * 3) return sz[i];
+    const auto t = [&](int s) {
+        return ((M + s - 1) / s) * ((N + s - 1) / s);
+    };
+    if (dt == TG_F32) {
+        for (int s : {128, 64})
+            if (t(s) * 4 >= (int64_t)cus * 3) return {s, 0};
+        return {32, 0};
     }
-    return sz[nsz - 1];
+    const int64_t nk = K * esize(dt) / 128, side = std::min(M, N);
+    if (side > 128 && t(128) > cus && (2 * t(256) >= cus || t(128) > 2 * cus))
+        return {256, 0};
+    if (side > 64 &&
+        t(128) * 20 >= (int64_t)cus * (dt == TG_BF16 ? 11 : 15))
+        return {128, t(128) > cus ? 2 : 0};
+    const bool deep = t(64) <= 2 * cus && nk >= 36;
+    if (deep || t(64) * 4 >= (int64_t)cus * 3) return {64, deep ? 4 : 2};
+    return {32, 0};
 }
 
 struct Launch {
@@ -549,8 +584,12 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
                         "aligned rows, K (and N for B stored K x N) a "
                         "multiple of 16 bytes, e4m3 B stored N x K");
         if (cfg.bm == 0 && cfg.bn == 0) {
-            int t = default_tile(L.gemm_dt, p.M, p.N, cus);
-            cfg.bm = cfg.bn = t;
+            const DefaultTile t =
+                default_tile(L.gemm_dt, p.M, p.N, L.Kc, cus);
+            cfg.bm = cfg.bn = t.size;
+            if (cfg.wm == 0 && cfg.wn == 0 && cfg.bk == 0 &&
+                cfg.stages == 0 && cfg.sched == 0)
+                cfg.stages = t.stages;
         } else if (cfg.bm == 0 || cfg.bn == 0) {
             return fail(TG_E_ARG, "config bm/bn: set both or neither");
         }

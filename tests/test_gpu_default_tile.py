@@ -1,0 +1,48 @@
+"""Default sub-tensor sizes of the tiled products on either side of the
+rule's lines (256 compute units): the size and LDS stages chosen, the product
+of small integers exact and every element stored once."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_util import exact64, note, reference
+
+pytestmark = pytest.mark.gpu
+
+tg = pytest.importorskip("paper_2606_15991_amd")
+DEV = "cuda:0"
+BF, F8 = torch.bfloat16, torch.float8_e4m3fn
+
+
+@pytest.mark.parametrize("dt,M,N,K,size,stages", [
+    (BF, 2816, 3072, 72, 256, 2),     # t(256) = 132 of 256
+    (BF, 2304, 2304, 72, 128, 2),     # t(256) = 81, t(128) = 324
+    (BF, 2048, 2048, 72, 128, 4),     # t(128) = 256
+    (BF, 129, 65536, 72, 256, 2), (BF, 128, 65536, 72, 128, 2),
+    (BF, 64, 65536, 72, 64, 2),       # at most 64 rows
+    (BF, 1408, 1664, 72, 128, 4),     # t(128) = 143 >= 140.8
+    (BF, 1408, 1536, 72, 64, 2),      # t(128) = 132, t(64) = 528
+    (F8, 1408, 1664, 144, 64, 2),     # e4m3: 128 from t(128) = 192 on
+    (F8, 1536, 2048, 144, 128, 2),
+    (BF, 130, 300, 2304, 64, 4), (BF, 130, 300, 2296, 32, 2),
+    (F8, 130, 300, 4608, 64, 4), (F8, 130, 300, 4592, 32, 2)])
+def test_default_tile_lines(dt, M, N, K, size, stages):
+    note("default tile", dt, M, N, K)
+    old = tg.tile_picker_mode(0)
+    try:
+        A = synth.small_int((M, K), 95).to(dt)
+        B = synth.small_int((N, K), 96).to(dt)
+        Ad, Bd = A.to(DEV), B.to(DEV)
+        C = torch.full((M, N), float("nan"), device=DEV)
+        wc = torch.zeros((M, N), dtype=torch.int32, device=DEV)
+        cfg = tg.tile_gemm_plan(Ad, Bd, C, b_trans=True, want_map=False)[0]
+        assert (cfg["bm"], cfg["stages"]) == (size, stages), cfg
+        tg.tile_gemm(Ad, Bd, C, b_trans=True, write_count=wc)
+        torch.cuda.synchronize()
+    finally:
+        tg.tile_picker_mode(old)
+    assert torch.all(wc == 1)
+    rows = np.unique(np.linspace(0, M - 1, 97).astype(int))
+    assert np.array_equal(exact64(C.cpu()[torch.from_numpy(rows)]),
+                          reference(A[rows], B, True))
