@@ -132,11 +132,14 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs &g,
     const int kb = sb * KSTEP;   // first element of this program's K range
     int s0 = 0;                  // first K step of the buffer contracted
     // NORM == 2: nw[kb, kb + (se - sb) KSTEP) into LDS as 16-byte chunks,
-    // zeros past K; run after the first weight loads are issued, so that
-    // its round trip overlaps theirs
+    // zeros past K, up to the end of the last super-step (its steps past se
+    // multiply zero activations with what stands here: a leftover NaN or
+    // infinity would not vanish); run after the first weight loads are
+    // issued, so that its round trip overlaps theirs
     auto stage_nw = [&]() {
         if constexpr (NORM == 2) {
-            const int chunks = (se - sb) * KSTEP / 8;
+            const int chunks =
+                (se - sb + UNROLL - 1) / UNROLL * UNROLL * KSTEP / 8;
             for (int i = threadIdx.x; i < chunks; i += KS * 64)
                 nw_lds[i] = ld_chunk(NWc, kb + 8 * i, g.K, 8, 2);
             __syncthreads();
