@@ -16,6 +16,8 @@ libtilegemm.so is missing the import of this package fails.
 """
 import ctypes
 import os
+import struct
+import threading
 
 import torch
 
@@ -259,8 +261,16 @@ def make_config(cfg) -> tg_config:
     return c
 
 
+# The current stream's handle without building a torch.cuda.Stream object
+# (0.2 us against 3.5); these need an initialised CUDA state.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:
+        if torch.cuda.is_initialized() and _raw_stream is not None:
+            return _raw_stream(_device())
         if torch.cuda.is_available():
             return torch.cuda.current_stream().cuda_stream
         return None
@@ -295,6 +305,102 @@ def make_opts(precision="native", scale_a=None, scale_b=None, config=None,
     return o
 
 
+class _Frame(ctypes.Structure):
+    """The descriptors of one call side by side, so that one pack fills
+    them (a descriptor object and its fields one by one cost a microsecond
+    each)."""
+    _fields_ = [("a", tg_in), ("b", tg_in), ("x", tg_in), ("c", tg_out),
+                ("o", tg_opts)]
+
+
+class _Call(threading.local):
+    """One frame per thread: the library reads it during the call and keeps
+    nothing of it."""
+
+    def __init__(self):
+        f = self.f = _Frame()
+        self.a, self.b, self.x = (ctypes.byref(f.a), ctypes.byref(f.b),
+                                  ctypes.byref(f.x))
+        self.c, self.o = ctypes.byref(f.c), ctypes.byref(f.o)
+        self.out = f.c
+        self.x_addr = ctypes.addressof(f.x)
+
+
+_call = _Call()
+_IN, _OUT, _OPTS = "Piiqqq", "Piiqqqii", "iiPPPPNPP"
+_pack = struct.Struct("@" + 3 * _IN + _OUT + _OPTS)
+assert _pack.size == ctypes.sizeof(_Frame)
+_NO_IN = (0, 0, 0, 0, 0, 0)
+
+
+def _in(t, trans=0):
+    """make_in's fields as a tuple."""
+    try:
+        dt = _DT[t.dtype]
+    except KeyError:
+        dt = dtype_code(t.dtype)          # raises
+    shape = t.shape
+    rows, cols = shape[0], shape[1]
+    if len(shape) != 2:
+        raise TileGemmError(TG_E_SHAPE, "operands are 2-D matrices")
+    ld, step = t.stride()
+    if cols > 1 and step != 1:
+        raise TileGemmError(TG_E_SHAPE, "rows must be contiguous")
+    if rows <= 1 and ld < cols:
+        ld = cols if cols > 1 else 1
+    return t.data_ptr(), dt, trans, rows, cols, ld
+
+
+def _opts(precision, checked, scale_a, scale_b, cfg, workspace, write_count,
+          residual):
+    """make_opts' fields as a tuple; cfg: a tg_config or None, residual: the
+    address of a tg_in or 0.  Pointers of None are 0."""
+    ws = n = 0
+    if workspace is not None:
+        ws = workspace.data_ptr()
+        n = workspace.numel() * workspace.element_size()
+    return (precision, 1 if checked else 0,
+            0 if scale_a is None else scale_a.data_ptr(),
+            0 if scale_b is None else scale_b.data_ptr(),
+            0 if cfg is None else ctypes.addressof(cfg), ws, n,
+            0 if write_count is None else write_count.data_ptr(), residual)
+
+
+def _precision(precision):
+    return PRECISIONS[precision] if isinstance(precision, str) \
+        else int(precision)
+
+
+def _gemm(entry, A, B, C, bm, bn, b_trans, precision, scale_a, scale_b,
+          config, workspace, alloc, write_count, checked, residual, stream):
+    """Fill the frame and call entry; returns the partition."""
+    k = _call
+    prec = _precision(precision)
+    cfg = None if config is None else make_config(config)   # (kept alive)
+    a, b, c = _in(A), _in(B, 1 if b_trans else 0), _in(C)
+    x, xa = _NO_IN, 0
+    if residual is not None:
+        x, xa = _in(residual), k.x_addr
+    h = _stream(stream)
+    out = c + (int(bm), int(bn))
+    o = _opts(prec, checked, scale_a, scale_b, cfg, workspace, write_count,
+              xa)
+    _pack.pack_into(k.f, 0, *a, *b, *x, *out, *o)
+    # only split precisions and decode products (at most 16 rows) take one
+    if alloc and workspace is None and (prec or a[3] <= 16):
+        need = lib.tile_gemm_workspace_size(k.a, k.b, k.c, k.o)
+        if need:
+            workspace = torch.empty(need, dtype=torch.uint8, device=C.device)
+            # (packed again: an allocation may run other code of this thread)
+            o = _opts(prec, checked, scale_a, scale_b, cfg, workspace,
+                      write_count, xa)
+            _pack.pack_into(k.f, 0, *a, *b, *x, *out, *o)
+    st = entry(k.a, k.b, k.c, k.o, h)
+    if st:
+        _raise(st)
+    return k.out.bm, k.out.bn
+
+
 def tile_gemm(A, B, C, bm=0, bn=0, *, b_trans=False, precision="native",
               scale_a=None, scale_b=None, config=None, workspace=None,
               write_count=None, checked=True, residual=None, stream=None):
@@ -305,18 +411,9 @@ def tile_gemm(A, B, C, bm=0, bn=0, *, b_trans=False, precision="native",
     decode products split along K over several programs need a workspace
     (allocated here from torch when not given).  Returns (A, B, C) -- the
     same tensor objects."""
-    da, db = make_in(A), make_in(B, b_trans)
-    dc = make_out(C, bm, bn)
-    o = make_opts(precision, scale_a, scale_b, config, workspace, write_count,
-                  checked, residual)
-    if workspace is None:
-        need = lib.tile_gemm_workspace_size(da, db, dc, o)
-        if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=C.device)
-            o.workspace = workspace.data_ptr()
-            o.workspace_bytes = need
-    _raise(lib.tile_gemm(da, db, dc, o, _stream(stream)))
-    tile_gemm.last_partition = (dc.bm, dc.bn)
+    tile_gemm.last_partition = _gemm(
+        lib.tile_gemm, A, B, C, bm, bn, b_trans, precision, scale_a, scale_b,
+        config, workspace, True, write_count, checked, residual, stream)
     return A, B, C
 
 
@@ -330,23 +427,29 @@ def tile_gemm_noalloc(A, B, C, bm=0, bn=0, *, b_trans=False,
     """tile_gemm without any device allocation: where tile_gemm takes a
     workspace the library's own per-device scratch is used (calls that
     overlap on one device race on it).  Returns (A, B, C)."""
-    da, db = make_in(A), make_in(B, b_trans)
-    dc = make_out(C, bm, bn)
-    o = make_opts(precision, scale_a, scale_b, config, None, write_count,
-                  checked, residual)
-    _raise(lib.tile_gemm_noalloc(da, db, dc, o, _stream(stream)))
-    tile_gemm_noalloc.last_partition = (dc.bm, dc.bn)
+    tile_gemm_noalloc.last_partition = _gemm(
+        lib.tile_gemm_noalloc, A, B, C, bm, bn, b_trans, precision, scale_a,
+        scale_b, config, None, False, write_count, checked, residual, stream)
     return A, B, C
+
+
+def _elementwise(entry, x, y, z, bm, bn, checked, write_count, stream):
+    k, h = _call, _stream(stream)
+    _pack.pack_into(k.f, 0, *_in(x), *_in(y), *_NO_IN, *_in(z), int(bm),
+                    int(bn), *_opts(TG_PREC_NATIVE, checked, None, None,
+                                    None, None, write_count, 0))
+    st = entry(k.a, k.b, k.c, k.o, h)
+    if st:
+        _raise(st)
+    return k.out.bm, k.out.bn
 
 
 def tile_add(x, y, z, bm=0, bn=0, *, checked=True, write_count=None,
              stream=None):
     """z = x + y element by element into z's bm x bn partition (bf16 or
     fp32, one shape and dtype for all three).  Returns z."""
-    dz = make_out(z, bm, bn)
-    o = make_opts(write_count=write_count, checked=checked)
-    _raise(lib.tile_add(make_in(x), make_in(y), dz, o, _stream(stream)))
-    tile_add.last_partition = (dz.bm, dz.bn)
+    tile_add.last_partition = _elementwise(
+        lib.tile_add, x, y, z, bm, bn, checked, write_count, stream)
     return z
 
 
@@ -354,10 +457,8 @@ def tile_mul(x, y, z, bm=0, bn=0, *, checked=True, write_count=None,
              stream=None):
     """z = x * y element by element into z's bm x bn partition (bf16 or
     fp32).  Returns z."""
-    dz = make_out(z, bm, bn)
-    o = make_opts(write_count=write_count, checked=checked)
-    _raise(lib.tile_mul(make_in(x), make_in(y), dz, o, _stream(stream)))
-    tile_mul.last_partition = (dz.bm, dz.bn)
+    tile_mul.last_partition = _elementwise(
+        lib.tile_mul, x, y, z, bm, bn, checked, write_count, stream)
     return z
 
 
@@ -367,11 +468,15 @@ def tile_rms_norm(x, w, y, eps=1e-6, bm=0, *, checked=True,
     elements, 1-D or 1 x d), into y's bm x d partition.  Returns y."""
     if w.dim() == 1:
         w = w.view(1, -1)
-    dy = make_out(y, bm, y.shape[1] if bm else 0)
-    o = make_opts(write_count=write_count, checked=checked)
-    _raise(lib.tile_rms_norm(make_in(x), make_in(w), float(eps), dy, o,
-                             _stream(stream)))
-    tile_rms_norm.last_partition = (dy.bm, dy.bn)
+    k, h = _call, _stream(stream)
+    _pack.pack_into(k.f, 0, *_in(x), *_in(w), *_NO_IN, *_in(y), int(bm),
+                    int(y.shape[1]) if bm else 0,
+                    *_opts(TG_PREC_NATIVE, checked, None, None, None, None,
+                           write_count, 0))
+    st = lib.tile_rms_norm(k.a, k.b, float(eps), k.c, k.o, h)
+    if st:
+        _raise(st)
+    tile_rms_norm.last_partition = (k.out.bm, k.out.bn)
     return y
 
 
@@ -390,18 +495,29 @@ def tile_rms_norm_matvec(x, nw, W, y, eps=1e-6, *, scale_w=None,
     when not given (workspace=False: no split).  Returns y."""
     if nw.dim() == 1:
         nw = nw.view(1, -1)
-    dy = make_out(y)
+    k = _call
+    a, w, n, out = _in(x), _in(W, 1), _in(nw), _in(y)
+    # the residual's descriptor is the one left without a place in the frame
+    res = None if residual is None else make_in(residual)
+    given = workspace if workspace is not None and workspace is not False \
+        else None
+    h = _stream(stream)
+
+    def fill():
+        _pack.pack_into(k.f, 0, *a, *w, *n, *out, 0, 0,
+                        *_opts(TG_PREC_NATIVE, checked, None, scale_w, None,
+                               given, write_count,
+                               0 if res is None else ctypes.addressof(res)))
+    fill()
     if workspace is None:
-        need = tile_rms_norm_matvec_workspace_size(x, W, y)
-        workspace = torch.empty(need, dtype=torch.uint8, device=y.device) \
-            if need else None
-    elif workspace is False:
-        workspace = None
-    o = make_opts(scale_b=scale_w, write_count=write_count, checked=checked,
-                  workspace=workspace, residual=residual)
-    _raise(lib.tile_rms_norm_matvec(make_in(x), make_in(nw), float(eps),
-                                    make_in(W, True), dy, o, _stream(stream)))
-    tile_rms_norm_matvec.last_partition = (dy.bm, dy.bn)
+        need = lib.tile_rms_norm_matvec_workspace_size(k.a, k.b, k.c)
+        if need:
+            given = torch.empty(need, dtype=torch.uint8, device=y.device)
+            fill()
+    st = lib.tile_rms_norm_matvec(k.a, k.x, float(eps), k.b, k.c, k.o, h)
+    if st:
+        _raise(st)
+    tile_rms_norm_matvec.last_partition = (k.out.bm, k.out.bn)
     return y
 
 

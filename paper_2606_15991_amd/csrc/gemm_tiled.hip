@@ -1731,15 +1731,23 @@ hipError_t launch_grouped(int variant, int n_problems, int total_tiles,
                            e.smem, st);
 }
 
+// (asked of the runtime once per variant: it depends on the compiled kernel
+// and the architecture alone)
 int tiled_occupancy(int variant) {
+    static std::atomic<int> known[128];
     int n;
     const VariantEntry &e = table(&n)[variant];
+    const bool keep = variant >= 0 && variant < 128;
+    if (keep)
+        if (const int k = known[variant].load(std::memory_order_relaxed))
+            return k;
     int blocks = 0;
     if (prepare_smem(e) != hipSuccess) return 1;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
             &blocks, e.kernel, e.threads, e.smem) != hipSuccess ||
         blocks < 1)
         return 1;
+    if (keep) known[variant].store(blocks, std::memory_order_relaxed);
     return blocks;
 }
 

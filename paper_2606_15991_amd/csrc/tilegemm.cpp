@@ -824,11 +824,11 @@ tg_status choose(const Problem &p, const tg_in *A, const tg_in *B,
     return choose_explicit(p, A, B, C, nullptr, L, have, norm);
 }
 
-// Program p -> owned sub-tensor ids, as the kernels walk them.
-void build_map(const Launch &L, int32_t *offs, int32_t *ids) {
+// Calls own(p, id) for every sub-tensor id of every program p, in the order
+// the kernels walk them; stops where own returns false.
+template <class Own>
+bool walk_map(const Launch &L, Own own) {
     const Sched &s = L.s;
-    int32_t q = 0;
-    offs[0] = 0;
     for (int32_t p = 0; p < s.n_prog; ++p) {
         if (L.cfg.kind == TG_KIND_SIMPLE) {
             int32_t bm, bn;
@@ -837,30 +837,61 @@ void build_map(const Launch &L, int32_t *offs, int32_t *ids) {
                  tm < std::min((bm + 1) * L.gm, s.tiles_m); ++tm)
                 for (int32_t tn = bn * L.gn;
                      tn < std::min((bn + 1) * L.gn, s.tiles_n); ++tn)
-                    ids[q++] = tm * s.tiles_n + tn;
+                    if (!own(p, tm * s.tiles_n + tn)) return false;
         } else if (L.cfg.kind == TG_KIND_TILED) {
             for (int32_t t = program_slot(p, s.n_prog); t < s.n_tiles;
                  t += s.n_prog) {
                 int32_t tm, tn;
                 tile_coords(t, s, tm, tn);
-                ids[q++] = tm * s.tiles_n + tn;
+                if (!own(p, tm * s.tiles_n + tn)) return false;
             }
-        } else {
-            ids[q++] = p;  // one program per sub-tensor, row-major grid
+        } else if (!own(p, p)) {   // one program per sub-tensor, row-major
+            return false;
         }
-        offs[p + 1] = q;
     }
+    return true;
 }
 
-// The program map a launch will walk, built into per-thread buffers that
-// are reused from call to call, checked with the rules of
-// tile_partition_check (injective, covering).
+// Program p -> owned sub-tensor ids.
+void build_map(const Launch &L, int32_t *offs, int32_t *ids) {
+    int32_t q = 0;
+    std::fill(offs, offs + L.s.n_prog + 1, 0);
+    walk_map(L, [&](int32_t p, int32_t id) {
+        ids[q++] = id;
+        offs[p + 1] = q;
+        return true;
+    });
+    for (int32_t p = 0; p < L.s.n_prog; ++p)
+        offs[p + 1] = std::max(offs[p + 1], offs[p]);
+}
+
+// The program map a launch will walk, checked with the rules of
+// tile_partition_check (injective, covering) as it is walked.
 tg_status check_launch_map(const Launch &L) {
-    static thread_local std::vector<int32_t> offs, ids;
-    offs.resize((size_t)L.s.n_prog + 1);
-    ids.resize((size_t)L.s.n_tiles);
-    build_map(L, offs.data(), ids.data());
-    return check_map(L.s.n_tiles, L.s.n_prog, offs.data(), ids.data());
+    // reused per thread: after the first call of a size, checking
+    // allocates nothing
+    static thread_local std::vector<uint8_t> seen;
+    const int32_t tiles = L.s.n_tiles;
+    if (L.s.n_prog == 0) return TG_OK;
+    seen.assign((size_t)tiles, 0);
+    int32_t owned = 0;
+    tg_status st = TG_OK;
+    walk_map(L, [&](int32_t p, int32_t t) {
+        if (t < 0 || t >= tiles)
+            st = fail(TG_E_ARG, "program %d: sub-tensor %d off the grid", p,
+                      t);
+        else if (seen[(size_t)t])
+            st = fail(TG_E_OVERLAP,
+                      "sub-tensor %d owned by two programs (second: %d)", t,
+                      p);
+        else
+            seen[(size_t)t] = 1, ++owned;
+        return st == TG_OK;
+    });
+    if (st == TG_OK && owned != tiles)
+        return fail(TG_E_NOCOVER, "%d of %d sub-tensors owned by no program",
+                    tiles - owned, tiles);
+    return st;
 }
 
 size_t split_bytes(const Problem &p, int np) {
