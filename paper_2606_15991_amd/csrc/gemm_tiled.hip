@@ -12,7 +12,7 @@
 //   * k-contiguous operands (A, and B stored N x K) live in LDS as
 //     [rows][128 B] with the 16-byte chunk index XOR-swizzled per row so
 //     that the 16-byte fragment reads are free of bank conflicts;
-//   * bf16 and e4m3 tiles move from HBM to LDS with direct buffer->LDS
+//   * tiles move from HBM to LDS with direct buffer->LDS
 //     loads (no staging registers, no LDS write instructions): lane l of a
 //     wavefront writes LDS bytes [16 l, 16 l + 16) of a 1 KiB block, so each
 //     lane fetches the global chunk that the swizzle assigns to that
@@ -27,11 +27,12 @@
 //     deeper ring with 32-deep tiles keeps the matrix cores fed); one barrier
 //     per K tile; the first K tiles of the program's next sub-tensor are
 //     fetched while the current one is stored;
-//   * f32 tiles go through registers (B stored K x N transposed 4 x 4 in
-//     registers), pipelined the same way;
-//   * in the f32 register path rows of A beyond M and columns of B beyond N
-//     are clamped to valid addresses (their products only reach outputs that
-//     are never stored) and the K tail is zero-filled.
+//   * a f32 B stored K x N stays k-major too and is read four bytes at a
+//     time, lanes along n (no bank conflicts).  The f32 product is bound by
+//     the 32x32x2 instruction (64 cycles each, 157 TFLOP/s nominal); what it
+//     lost was waiting: tiles staged through registers at one program per
+//     compute unit ran 2048^3 in 171 us and 3072^3 in 815, direct loads 141
+//     and 475 (the chip's rate on a large f32 product: 121 and 407).
 #include <atomic>
 #include <iterator>
 #include <vector>
@@ -40,96 +41,6 @@
 
 namespace tg {
 namespace {
-
-// Register-staged K tile of the f32 path.  load() issues the global reads,
-// store() writes LDS.
-template <class C>
-struct RegTile {
-    uint4 ra[C::A_CH];
-    static_assert(!C::DIRECT, "register staging is the f32 path");
-    uint4 rb[C::BNK ? C::B_CH : C::B_BLK_PT * C::EPC];
-
-    template <bool MASK>
-    __device__ __forceinline__ void load(const Job &j, int k0, int tid) {
-#pragma unroll
-        for (int i = 0; i < C::A_CH; ++i) {
-            const int q = i * C::THREADS + tid;
-            int row = j.m0 + (q >> 3);
-            row = row < j.M ? row : j.M - 1;
-            const int k = k0 + (q & 7) * C::EPC;
-            if (MASK && k >= j.K)
-                ra[i] = uint4{0, 0, 0, 0};
-            else
-                ra[i] = ld16(j.a + ((int64_t)row * j.lda + k) * C::ES);
-        }
-        if constexpr (C::BNK) {
-#pragma unroll
-            for (int i = 0; i < C::B_CH; ++i) {
-                const int q = i * C::THREADS + tid;
-                int row = j.n0 + (q >> 3);
-                row = row < j.N ? row : j.N - 1;
-                const int k = k0 + (q & 7) * C::EPC;
-                if (MASK && k >= j.K)
-                    rb[i] = uint4{0, 0, 0, 0};
-                else
-                    rb[i] = ld16(j.b + ((int64_t)row * j.ldb + k) * C::ES);
-            }
-        } else {
-            constexpr int NB = C::BN / C::EPC;
-#pragma unroll
-            for (int i = 0; i < C::B_BLK_PT; ++i) {
-                const int blk = i * C::THREADS + tid;
-                if (C::B_BLK % C::THREADS != 0 && blk >= C::B_BLK) break;
-                const int kb = blk / NB, nb = blk % NB;
-                int col = j.n0 + nb * C::EPC;
-                col = col < j.N ? col : j.N - C::EPC;
-#pragma unroll
-                for (int r = 0; r < C::EPC; ++r) {
-                    const int k = k0 + kb * C::EPC + r;
-                    if (MASK && k >= j.K)
-                        rb[i * C::EPC + r] = uint4{0, 0, 0, 0};
-                    else
-                        rb[i * C::EPC + r] =
-                            ld16(j.b + ((int64_t)k * j.ldb + col) * C::ES);
-                }
-            }
-        }
-    }
-
-    __device__ __forceinline__ void store(char *stage, int tid) {
-        char *As = stage;
-        char *Bs = stage + C::BM * C::RBY;
-#pragma unroll
-        for (int i = 0; i < C::A_CH; ++i) {
-            const int q = i * C::THREADS + tid;
-            st16(As + swz<C>(q >> 3, q & 7), ra[i]);
-        }
-        if constexpr (C::BNK) {
-#pragma unroll
-            for (int i = 0; i < C::B_CH; ++i) {
-                const int q = i * C::THREADS + tid;
-                st16(Bs + swz<C>(q >> 3, q & 7), rb[i]);
-            }
-        } else {
-            // f32 B stored K x N: 4 x 4 blocks (rows k, columns n) become
-            // chunks (n, k .. k+3)
-            constexpr int NB = C::BN / C::EPC;
-#pragma unroll
-            for (int i = 0; i < C::B_BLK_PT; ++i) {
-                const int blk = i * C::THREADS + tid;
-                if (C::B_BLK % C::THREADS != 0 && blk >= C::B_BLK) break;
-                const int kb = blk / NB, nb = blk % NB;
-                const uint32_t *w =
-                    reinterpret_cast<const uint32_t *>(&rb[i * C::EPC]);
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    st16(Bs + swz<C>(nb * 4 + c, kb),
-                         uint4{w[0 * 4 + c], w[1 * 4 + c], w[2 * 4 + c],
-                               w[3 * 4 + c]});
-            }
-        }
-    }
-};
 
 // ---------------------------------------------------------------- compute
 
@@ -160,7 +71,14 @@ __device__ __forceinline__ void compute_stage(const char *stage, int wm,
                     Aw + f * 32 * C::RBY + co);
 #pragma unroll
             for (int f = 0; f < C::FN; ++f) {
-                if constexpr (C::B_KMAJOR)
+                if constexpr (C::B_KMAJOR && C::DTYPE == TG_F32) {
+                    // k = 8 kk + 4 half + e, as the A chunk of this half
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        bfr[s][f][e] = *reinterpret_cast<const int *>(
+                            Bs + (8 * kk + 4 * half + e) * C::RB +
+                            (wn * C::TN + f * 32 + r) * 4);
+                } else if constexpr (C::B_KMAJOR)
                     bfr[s][f] = read_b_kmajor<C>(Bs, kk, wn * C::TN + f * 32,
                                                  lane);
                 else
@@ -752,43 +670,6 @@ __device__ __forceinline__ void run_direct_xh(const P &prov, char *smem) {
     }
 }
 
-// Register-staged programs (f32).
-template <class C, class P>
-__device__ __forceinline__ void run_regs(const P &prov, char *smem) {
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
-    const int wm = wave / C::WN, wn = wave % C::WN;
-    const int G = prov.n_prog(), total = prov.count();
-    f32x16 acc[C::FM][C::FN];
-    for (int t = program_slot(blockIdx.x, G); t < total; t += G) {
-        const Job j = prov.job(t);
-        zero_acc<C>(acc);
-        const int nk_full = j.K / C::BK;
-        const int nk = nk_full + (j.K % C::BK != 0);
-        RegTile<C> rt;
-        if (nk > 0) {
-            if (nk_full > 0)
-                rt.template load<false>(j, 0, tid);
-            else
-                rt.template load<true>(j, 0, tid);
-            rt.store(smem, tid);
-            __syncthreads();
-        }
-        for (int kt = 0; kt < nk; ++kt) {
-            const int nxt = kt + 1;
-            if (nxt < nk_full)
-                rt.template load<false>(j, nxt * C::BK, tid);
-            else if (nxt < nk)
-                rt.template load<true>(j, nxt * C::BK, tid);
-            compute_stage<C>(smem + (kt & 1) * C::STAGE, wm, wn, lane, acc,
-                             [](int, int) {});
-            if (nxt < nk) rt.store(smem + (nxt & 1) * C::STAGE, tid);
-            __syncthreads();
-        }
-        epilogue<C>(j, wm, wn, lane, acc, nullptr);
-    }
-}
 
 // ------------------------------------------------------ ping-pong schedule
 //
@@ -1550,10 +1431,8 @@ __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE))) void gemm_tiled_kernel(
         run_direct_xh<C>(p, smem);
     else if constexpr (C::XT)
         run_direct_xt<C>(p, smem);
-    else if constexpr (C::DIRECT)
-        run_direct<C>(p, smem);
     else
-        run_regs<C>(p, smem);
+        run_direct<C>(p, smem);
 }
 
 template <class C>
@@ -1574,10 +1453,8 @@ __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE))) void gemm_grouped_kernel(
         run_direct_xh<C>(p, smem);
     else if constexpr (C::XT)
         run_direct_xt<C>(p, smem);
-    else if constexpr (C::DIRECT)
-        run_direct<C>(p, smem);
     else
-        run_regs<C>(p, smem);
+        run_direct<C>(p, smem);
 }
 
 template <class C>
@@ -1655,6 +1532,9 @@ std::vector<VariantEntry> all_entries() {
         TG_VARIANTS_FOR(TG_BF16, 64, 64, 2, 2, 128, 2),
         TG_VARIANTS_FOR(TG_BF16, 64, 64, 2, 2, 128, 4),
         TG_VARIANTS_FOR(TG_BF16, 32, 32, 1, 1, 128, 2),
+        // eight wavefronts: two per SIMD, one contracts while the other waits
+        // (2048^3 141.5 us against 144.2 with four)
+        TG_VARIANTS_FOR(TG_F32, 128, 128, 2, 4, 128, 2),
         TG_VARIANTS_FOR(TG_F32, 128, 128, 2, 2, 128, 2),
         TG_VARIANTS_FOR(TG_F32, 64, 64, 2, 2, 128, 2),
         TG_VARIANTS_FOR(TG_F32, 32, 32, 1, 1, 128, 2),

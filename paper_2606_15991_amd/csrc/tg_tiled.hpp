@@ -62,15 +62,9 @@ struct Cfg {
     static constexpr int THREADS = NW * 64;
     static constexpr int TM = BM / WM, TN = BN / WN;
     static constexpr int FM = TM / 32, FN = TN / 32;
-    static constexpr bool DIRECT = ES <= 2;     // direct buffer->LDS loads
-    static constexpr bool B_KMAJOR = !BNK && ES == 2;  // [BK][BN] in LDS
+    static constexpr bool B_KMAJOR = !BNK && ES >= 2;  // [BK][BN] in LDS
     static constexpr int RB = BN * ES;          // bytes per k-major B row
     static constexpr int CPR = RB / 16;         // chunks per k-major B row
-    static constexpr int A_CH = BM * 8 / THREADS;   // f32 path: A chunks
-    static constexpr int B_CH = BN * 8 / THREADS;   // f32 path: B chunks
-    // f32 B stored K x N: EPC x EPC blocks, (BK / EPC) * (BN / EPC) of them
-    static constexpr int B_BLK = (BK / EPC) * (BN / EPC);
-    static constexpr int B_BLK_PT = (B_BLK + THREADS - 1) / THREADS;
     static constexpr int STAGE = (BM + BN) * RBY;   // bytes per LDS stage
     // Per-row and per-column scales of an owned sub-tensor live in LDS next
     // to the stages, one slot per sub-tensor in flight (NS + 1 slots: the
@@ -79,7 +73,7 @@ struct Cfg {
     static constexpr int NSLOT = NS + 1;
     static constexpr int SMEM =
         (XT && NS == 3 ? 5 * (STAGE / 2) : NS * STAGE) +
-        (DIRECT && !XT && SCH_ != TG_SCHED_STAGED &&
+        (!XT && SCH_ != TG_SCHED_STAGED &&
                  SCH_ != TG_SCHED_BULK
              ? NSLOT * SCALE_SLOT
              : 0);
@@ -96,12 +90,9 @@ struct Cfg {
     // NS = 3 with the cross-tile schedule: the LDS holds five operand
     // tiles (A or B of one K tile each) instead of three whole stages.
     static constexpr bool HALVES = XT && NS == 3;
-    static_assert(DIRECT || (RBY == 128 && NS == 2), "f32 register path");
     static_assert((BM / RPK) % NW == 0, "A 1 KiB blocks per wave");
     static_assert(B_KMAJOR ? (BK * RB / 1024) % NW == 0
                            : (BN / RPK) % NW == 0, "B 1 KiB blocks per wave");
-    static_assert(DIRECT || ((BM * 8) % THREADS == 0 &&
-                             (BN * 8) % THREADS == 0), "f32 chunk split");
     static_assert(BNK || DT != TG_FP8_E4M3, "e4m3 B must be stored N x K");
     static_assert(!B_KMAJOR || CPR >= 4, "k-major B rows of >= 64 bytes");
     static_assert(DT != TG_FP8_E4M3 || BK >= 64, "e4m3 K tile >= 64");
@@ -112,11 +103,11 @@ struct Cfg {
     // trades the fragment double buffer for fewer registers.
     static constexpr int WG_PER_CU_ = 163840 / SMEM;
     static constexpr int WPE_ = WG_PER_CU_ * NW / 4;
-    static constexpr int WPE_MAX_ = DIRECT ? 4 : 2;  // f32: register staging
+    static constexpr int WPE_MAX_ = 4;
     static constexpr int WPE = WPE_ < 1 ? 1 : (WPE_ > WPE_MAX_ ? WPE_MAX_ : WPE_);
-    static_assert(!PP || (DIRECT && WM == 2 && NW == 8 && NS >= 3),
+    static_assert(!PP || (WM == 2 && NW == 8 && NS >= 3),
                   "ping-pong: two groups of four wavefronts, >= 3 stages");
-    static_assert(!XT || DIRECT, "cross-tile schedule: bf16 or e4m3");
+    static_assert(!XT || ES <= 2, "cross-tile schedule: bf16 or e4m3");
     static_assert(!BLK || (DT == TG_BF16 && BNK && NS >= 4 &&
                            BK / 16 * (FM + FN) * 4 <= 128),
                   "bulk schedule: bf16, B stored N x K, a ring of at least "
@@ -151,6 +142,7 @@ __device__ __forceinline__ int swz(int row, int chunk) {
 // 16-byte bank groups.
 template <class C>
 __device__ __forceinline__ int swz_kmajor(int k) {
+    if constexpr (C::ES == 4) return 0;   // binary32: plain dword reads
     if constexpr (C::CPR >= 16) {
         constexpr uint32_t tab = 0u | (4u << 8) | (10u << 16) | (14u << 24);
         return (tab >> (8 * (k & 3))) & 0xff;

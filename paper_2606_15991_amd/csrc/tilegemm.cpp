@@ -225,7 +225,7 @@ bool tiled_ok(const Problem &p, const tg_in *A, const tg_in *B,
     if ((A->rows > 1 && (A->ld * es) % 16) || (B->rows > 1 && (B->ld * es) % 16))
         return false;
     // bf16 / e4m3 take any K (the straddling chunk is filled element-wise);
-    // the f32 register path needs whole 16-byte chunks
+    // f32 needs whole 16-byte chunks
     if (dt == TG_F32 && p.K % epc) return false;
     if (!p.b_nk && (p.N % epc)) return false;
     // the kernels address a sub-tensor with 32-bit byte offsets: 256 rows of
@@ -299,7 +299,14 @@ int64_t tiles_of(int64_t M, int64_t N, int s) {
 //      1536^3 (t(64) = 576) 31.5 against 22.6 and e4m3 200 x 300 x 4000 (31
 //      K tiles) 15.8 against 14.8;
 //  32 where 64 leaves a quarter of the compute units idle and K is shorter.
-// f32: the largest that gives three in four compute units a sub-tensor.
+// f32 is bound by the matrix instructions alone, so the busiest compute unit
+// decides: ceil(t / cus) rounds at 36 us (64) and 128 us (128) for K = 2048:
+//  128 where two of its rounds take no longer than seven of 64: 2048^3 (1 and
+//      4 rounds) 141 us against 145, 4096^3 (4 and 16) 1025 against 1098;
+//  64  else: 3072^3 (9 rounds, 128: 3) 475 us against 578, 512 x 5120 x 5120
+//      (3, 1) 275 against 342, 1000 x 3000 x 2000 (3, 1) 112 against 138;
+//  32 is never ahead (512^3 16.5 us against 15.6, 130 x 3000 x 256 10.0
+//      against 9.7) and is left to outputs of at most 32 rows or columns.
 struct DefaultTile {
     int size, stages;
 };
@@ -309,9 +316,9 @@ DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, int cus) {
         return ((M + s - 1) / s) * ((N + s - 1) / s);
     };
     if (dt == TG_F32) {
-        for (int s : {128, 64})
-            if (t(s) * 4 >= (int64_t)cus * 3) return {s, 0};
-        return {32, 0};
+        const auto rounds = [&](int s) { return (t(s) + cus - 1) / cus; };
+        if (std::min(M, N) <= 32) return {32, 0};
+        return {2 * rounds(64) >= 7 * rounds(128) ? 128 : 64, 0};
     }
     const int64_t nk = K * esize(dt) / 128, side = std::min(M, N);
     if (side > 128 && t(128) > cus && (2 * t(256) >= cus || t(128) > 2 * cus))
@@ -628,7 +635,13 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
         L.s.n_tiles = L.s.tiles_m * L.s.tiles_n;
         int occ = cus > 0 ? tiled_occupancy(L.variant) : 1;
         int64_t cap = (int64_t)(cus > 0 ? cus : 256) * occ;
-        L.s.n_prog = (int32_t)std::min<int64_t>(L.s.n_tiles, cap);
+        // binary32: one program per sub-tensor.  Its matrix instructions take
+        // 32 times as long per byte as the bf16 ones, so loads need no
+        // stream across sub-tensors, and the dispatcher levels an uneven
+        // last round that a fixed deal leaves on two of the eight XCDs.
+        L.s.n_prog = L.gemm_dt == TG_F32
+                         ? L.s.n_tiles
+                         : (int32_t)std::min<int64_t>(L.s.n_tiles, cap);
         L.s.group_m = 8;
     } else {  // simple
         if (np > 1)

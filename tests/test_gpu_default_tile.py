@@ -12,7 +12,33 @@ pytestmark = pytest.mark.gpu
 
 tg = pytest.importorskip("paper_2606_15991_amd")
 DEV = "cuda:0"
-BF, F8 = torch.bfloat16, torch.float8_e4m3fn
+BF, F8, F32 = torch.bfloat16, torch.float8_e4m3fn, torch.float32
+
+
+@pytest.mark.parametrize("tile", [128, 64, 32])
+@pytest.mark.parametrize("nk", [True, False])
+@pytest.mark.parametrize("M,N,K", [(131, 260, 4), (129, 132, 100),
+                                   (40, 516, 32), (257, 384, 68)])
+def test_f32_tiles(tile, nk, M, N, K):
+    """Rows, columns and K tiles cut off by the operands' ends, which lie in
+    larger buffers of NaN; small integers, exact."""
+    note("f32 tile", tile, nk, M, N, K)
+    A = synth.small_int((M, K), 97).float()
+    B = synth.small_int((N, K) if nk else (K, N), 98).float()
+
+    def inside(x):
+        big = torch.full((x.shape[0] + 2, x.shape[1] + 12), float("nan"),
+                         device=DEV)
+        v = big[1:-1, 4:4 + x.shape[1]]
+        v.copy_(x)
+        return v
+    C = torch.full((M, N), float("nan"), device=DEV)
+    wc = torch.zeros((M, N), dtype=torch.int32, device=DEV)
+    tg.tile_gemm(inside(A), inside(B), C, b_trans=nk, config=dict(
+        kind="tiled", bm=tile, bn=tile), write_count=wc)
+    torch.cuda.synchronize()
+    assert torch.all(wc == 1)
+    assert np.array_equal(exact64(C.cpu()), reference(A, B, nk))
 
 
 @pytest.mark.parametrize("dt,M,N,K,size,stages", [
@@ -26,7 +52,10 @@ BF, F8 = torch.bfloat16, torch.float8_e4m3fn
     (F8, 1408, 1664, 144, 64, 2),     # e4m3: 128 from t(128) = 192 on
     (F8, 1536, 2048, 144, 128, 2),
     (BF, 130, 300, 2304, 64, 4), (BF, 130, 300, 2296, 32, 2),
-    (F8, 130, 300, 4608, 64, 4), (F8, 130, 300, 4592, 32, 2)])
+    (F8, 130, 300, 4608, 64, 4), (F8, 130, 300, 4592, 32, 2),
+    (F32, 32, 20000, 36, 32, 2), (F32, 33, 20000, 36, 64, 2),
+    (F32, 2048, 1536, 36, 64, 2),     # three rounds of 64, one of 128
+    (F32, 2048, 1540, 4, 128, 2)])    # four, one
 def test_default_tile_lines(dt, M, N, K, size, stages):
     note("default tile", dt, M, N, K)
     old = tg.tile_picker_mode(0)
