@@ -119,7 +119,11 @@ __device__ __forceinline__ void ph_dma2(const i32x4 &srd, uint32_t base,
         : "memory", "scc");
 }
 
-template <class C>
+// PL: the operands are planes of a split binary32 product, side by side
+// along K (K % 64 == 0 elements each), and the K loop runs over products of
+// planes: block b of kp elements multiplies plane a of A and plane b of B as
+// GemmArgs says.  A plane that several products read is stored once.
+template <class C, bool PL = false>
 struct Phased {
     static_assert(C::BM == 256 && C::BN == 256 && C::RBY == 128 &&
                       C::NW == 8 && C::WM == 2 && C::FM == 4 && C::FN == 2,
@@ -147,6 +151,11 @@ struct Phased {
     i32x4 sa, sb;
     uint32_t va[2][2], vb[2][2];
     int nk, head;     // K tiles; 1 when tile 0 of the sequence is K's tail
+    // PL: byte offsets along K of the product tile that is loaded next (and
+    // of A's tile before it), bytes of a plane, K tiles left of the current
+    // product and the products still to come
+    int soa1, soa, sob, kpb, left_pl;
+    uint32_t ord_a, ord_b;
 
     // The K tiles of a sub-tensor in the order they are contracted: a
     // partial last tile comes first, so that all later loads are whole.
@@ -246,6 +255,20 @@ struct Phased {
     __device__ __forceinline__ int soff(int q) const {
         return (q - head) << 7;
     }
+    // PL: offsets of the first product's first tile, and on to the next.
+    __device__ __forceinline__ void next_product() {
+        soa = (int)(ord_a & 0xf) * kpb;
+        sob = (int)(ord_b & 0xf) * kpb;
+        ord_a >>= 4;
+        ord_b >>= 4;
+        left_pl = kpb >> 7;
+    }
+    __device__ __forceinline__ void next_offsets() {
+        soa1 = soa;
+        soa += 128;
+        sob += 128;
+        if (--left_pl == 0) next_product();
+    }
     // Half H of A / B into stage S, K offset so (row mode; k-major: srd is
     // the tile's own descriptor).
     template <int S, int H>
@@ -256,11 +279,11 @@ struct Phased {
     __device__ __forceinline__ void issue_b(int so) const {
         ph_dma2<S * C::STAGE + (2 + H) * HALF>(sb, lbase, vb[H], so);
     }
-    // Descriptor of sequence tile q >= 1 of a k-major B: all its rows lie
+    // Descriptor of a k-major B from offset so along K, not tile 0's: all its rows lie
     // inside K, columns past N are masked by their offsets.
-    __device__ __forceinline__ void kmajor_tile(int q) {
+    __device__ __forceinline__ void kmajor_tile(int so) {
         if constexpr (C::B_KMAJOR)
-            sb = make_srd(j.b_row + (int64_t)k0_of(q) * j.ldb * C::ES,
+            sb = make_srd(j.b_row + (int64_t)(so / C::ES) * j.ldb * C::ES,
                           0x7fffffffu);
     }
     __device__ __forceinline__ int bsoff(int so) const {
@@ -269,15 +292,16 @@ struct Phased {
     // tile 0 of the sequence, possibly K's tail: chunks not wholly inside K
     // load as zeros
     __device__ __forceinline__ void issue_tile0() {
-        const int k0 = k0_of(0), so = k0 * C::ES;
+        const int k0 = PL ? 0 : k0_of(0);
+        const int oa = PL ? soa : k0 * C::ES, ob = PL ? sob : k0 * C::ES;
         constexpr bool KM = C::B_KMAJOR;
         i32x4 b0 = sb;
         if constexpr (KM) {
-            const int64_t skip = (int64_t)k0 * j.ldb * C::ES;
+            const int64_t skip = (int64_t)(ob / C::ES) * j.ldb * C::ES;
             b0 = make_srd(j.b_row + skip, sat_bytes(j.b_rem - skip));
         }
         auto put = [&](auto D, const i32x4 &srd, const uint32_t (&v)[2],
-                       bool rows_of_k) {
+                       bool rows_of_k, int so) {
             uint32_t w[2] = {v[0], v[1]};
             if (!rows_of_k) {
                 if (!chunk_in(0, k0)) w[0] = kOutOfRange;
@@ -285,10 +309,10 @@ struct Phased {
             }
             ph_dma2<D.value>(srd, lbase, w, rows_of_k ? 0 : so);
         };
-        put(Int<2 * HALF>{}, b0, vb[0], KM);
-        put(Int<0>{}, sa, va[0], false);
-        put(Int<3 * HALF>{}, b0, vb[1], KM);
-        put(Int<HALF>{}, sa, va[1], false);
+        put(Int<2 * HALF>{}, b0, vb[0], KM, ob);
+        put(Int<0>{}, sa, va[0], false, oa);
+        put(Int<3 * HALF>{}, b0, vb[1], KM, ob);
+        put(Int<HALF>{}, sa, va[1], false, oa);
     }
     __device__ __forceinline__ bool chunk_in(int i, int k0) const {
         const int lr = (i * 8 + wave) * 8 + (lane >> 3);
@@ -299,12 +323,15 @@ struct Phased {
     // half 1
     __device__ __forceinline__ void issue_first() {
         if (nk > 0) issue_tile0();
+        if constexpr (PL) next_offsets();
         if (nk > 1) {
-            kmajor_tile(1);
-            issue_b<1, 0>(bsoff(soff(1)));
-            issue_a<1, 0>(soff(1));
-            issue_b<1, 1>(bsoff(soff(1)));
+            const int oa = PL ? soa : soff(1), ob = PL ? sob : soff(1);
+            kmajor_tile(ob);
+            issue_b<1, 0>(bsoff(ob));
+            issue_a<1, 0>(oa);
+            issue_b<1, 1>(bsoff(ob));
         }
+        if constexpr (PL) next_offsets();
     }
     // The chunk that straddles K was loaded as zeros: its K % EPC valid
     // elements of every row, one by one.
@@ -428,8 +455,9 @@ struct Phased {
         }
     }
     // K tile of the sequence in stage S, `left` tiles to go with it; x holds
-    // its B half 0, and at the end y holds the next tile's.  q: sequence
-    // index of the tile two further on, so: its byte offset along K.
+    // its B half 0, and at the end y holds the next tile's.  so_a1, so_a and
+    // so_b: offsets along K of A's next tile and of both operands' tile two
+    // further on.
     //
     // Reuse: a half read in memory slot i by the first group is read in the
     // next slot by the second, whose data have arrived by the end of its
@@ -439,24 +467,26 @@ struct Phased {
     // 1 in phase 4, A half 1 in phase 1 of the next tile.
     template <int S>
     __device__ __forceinline__ void tile(FA &a, FB &x, FB &y, Acc &acc,
-                                         int left, int q, int so) {
+                                         int left, int so_a1, int so_a,
+                                         int so_b) {
         read_a<S>(a, 0);
-        if (__builtin_expect(left > 1, 1)) issue_a<1 - S, 1>(so - 128);
+        if (__builtin_expect(left > 1, 1)) issue_a<1 - S, 1>(so_a1);
         wait_loads<10, 2>(left);
         slots<0, 0>(a, x, acc);
         read_b<S>(y, 1);
         if (__builtin_expect(left > 2, 1)) {
-            kmajor_tile(q);
-            issue_b<S, 0>(bsoff(so));
+            kmajor_tile(so_b);
+            issue_b<S, 0>(bsoff(so_b));
         }
         wait_loads<8, 0>(left);
         slots<0, 1>(a, y, acc);
         read_a<S>(a, 1);
-        if (__builtin_expect(left > 2, 1)) issue_a<S, 0>(so);
+        if (__builtin_expect(left > 2, 1)) issue_a<S, 0>(so_a);
         wait_loads<6, 0>(left);
         slots<1, 1>(a, y, acc);
         read_b<1 - S>(y, 0);
-        if (__builtin_expect(left > 2, 1)) issue_b<S, 1>(bsoff(so));
+        if (__builtin_expect(left > 2, 1)) issue_b<S, 1>(bsoff(so_b));
+        if constexpr (PL) next_offsets();
         wait_loads<4, 0>(left);
         slots<1, 0>(a, x, acc);
     }
@@ -618,6 +648,15 @@ struct Phased {
     }
 
     template <class P>
+    __device__ __forceinline__ void start_offsets(const P &prov) {
+        if constexpr (PL) {
+            ord_a = prov.g.planes_a;
+            ord_b = prov.g.planes_b;
+            kpb = prov.g.kp * C::ES;
+            next_product();
+        }
+    }
+    template <class P>
     __device__ __forceinline__ void run(const P &prov, char *s) {
         const int G = prov.n_prog(), total = prov.count();
         int t = program_slot(blockIdx.x, G);
@@ -628,6 +667,7 @@ struct Phased {
         FA a;
         FB x, y;
         set_job(prov.job(t));
+        start_offsets(prov);
         tg::issue_scales<C>(j, scale_slot<C>(smem, 0), wave, lane);
         issue_first();
         while (true) {
@@ -645,9 +685,11 @@ struct Phased {
                 if (wm) slot_end();       // one slot behind
                 int so = soff(2);
                 for (int left = nk;; left -= 2, so += 256) {
-                    tile<0>(a, x, y, acc, left, nk - left + 2, so);
+                    tile<0>(a, x, y, acc, left, PL ? soa1 : so - 128,
+                            PL ? soa : so, PL ? sob : so);
                     if (left == 1) break;
-                    tile<1>(a, y, x, acc, left - 1, nk - left + 3, so + 128);
+                    tile<1>(a, y, x, acc, left - 1, PL ? soa1 : so,
+                            PL ? soa : so + 128, PL ? sob : so + 128);
                     if (left == 2) break;
                 }
                 if (!wm) slot_end();      // level again: LDS is free
@@ -658,6 +700,7 @@ struct Phased {
             const Job done = j;
             if (more) {
                 set_job(prov.job(t));
+                start_offsets(prov);
                 tg::issue_scales<C>(j, scale_slot<C>(smem, njob + 1), wave,
                                     lane);
                 issue_first();
@@ -672,13 +715,13 @@ struct Phased {
     }
 };
 
-template <class C>
+template <class C, bool PL>
 __global__ __launch_bounds__(512)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_phased_kernel(
     GemmArgs g) {
     extern __shared__ __align__(1024) char smem[];
     SingleProvider<C> p{g};
-    Phased<C> k;
+    Phased<C, PL> k;
     k.run(p, smem);
 }
 
@@ -695,13 +738,16 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_phased_grouped_kernel(
 template <int DT, bool BNK, bool CBF16>
 VariantEntry entry(int sched = TG_SCHED_CROSS) {
     typedef Cfg<DT, 256, 256, 2, 4, BNK, CBF16, 128, 2, TG_SCHED_CROSS> C;
-    VariantEntry e;
+    VariantEntry e{};
     e.v.dtype = DT;
     e.v.bm = C::BM; e.v.bn = C::BN; e.v.bk = C::BK; e.v.stages = C::NS;
     e.v.sched = sched;
     e.v.wm = C::WM; e.v.wn = C::WN;
     e.v.b_nk = BNK; e.v.c_bf16 = CBF16;
-    e.kernel = reinterpret_cast<const void *>(&gemm_phased_kernel<C>);
+    e.kernel = reinterpret_cast<const void *>(&gemm_phased_kernel<C, false>);
+    if constexpr (DT == TG_BF16)
+        e.planes =
+            reinterpret_cast<const void *>(&gemm_phased_kernel<C, true>);
     e.grouped = reinterpret_cast<const void *>(&gemm_phased_grouped_kernel<C>);
     e.threads = C::THREADS;
     e.smem = Phased<C>::SMEM;

@@ -1583,9 +1583,17 @@ static hipError_t prepare_smem(const VariantEntry &e) {
     if (err == hipSuccess)
         err = hipFuncSetAttribute(
             e.grouped, hipFuncAttributeMaxDynamicSharedMemorySize, e.smem);
+    if (err == hipSuccess && e.planes)
+        err = hipFuncSetAttribute(
+            e.planes, hipFuncAttributeMaxDynamicSharedMemorySize, e.smem);
     if (err == hipSuccess && idx >= 0 && idx < 128)
         done[idx].store(1, std::memory_order_release);
     return err;
+}
+
+bool tiled_planes(int variant) {
+    int n;
+    return table(&n)[variant].planes != nullptr;
 }
 
 hipError_t launch_tiled(int variant, const GemmArgs &args, hipStream_t st) {
@@ -1594,8 +1602,9 @@ hipError_t launch_tiled(int variant, const GemmArgs &args, hipStream_t st) {
     hipError_t err = prepare_smem(e);
     if (err != hipSuccess) return err;
     void *params[] = {const_cast<GemmArgs *>(&args)};
-    return hipLaunchKernel(e.kernel, dim3(args.s.n_prog), dim3(e.threads),
-                           params, e.smem, st);
+    return hipLaunchKernel(args.kp ? e.planes : e.kernel,
+                           dim3(args.s.n_prog), dim3(e.threads), params,
+                           e.smem, st);
 }
 
 hipError_t launch_grouped(int variant, int n_problems, int total_tiles,

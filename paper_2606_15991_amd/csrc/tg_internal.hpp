@@ -75,6 +75,11 @@ struct GemmArgs {
     int64_t lda, ldb, ldc;
     int32_t M, N, K;
     Sched s;
+    // Products of planes: kp > 0 elements of K per plane, planes side by side
+    // along K in A and B; product b (of K / kp) multiplies the planes that
+    // four-bit field b of planes_a and planes_b names.
+    int32_t kp = 0;
+    uint32_t planes_a = 0, planes_b = 0;
 };
 
 // One problem of a grouped launch (device-side table entry).
@@ -107,6 +112,8 @@ const TiledVariant &tiled_variant(int i);
 hipError_t launch_tiled(int variant, const GemmArgs &args, hipStream_t st);
 hipError_t launch_grouped(int variant, int n, int total_tiles, int n_prog,
                           const void *table_dev, hipStream_t st);
+// Whether variant i also runs products of planes (kp != 0).
+bool tiled_planes(int variant);
 int tiled_occupancy(int variant);  // resident workgroups per CU
 
 // Skinny (decode-shaped) kernel.
@@ -163,10 +170,16 @@ struct SimpleArgs {
 hipError_t launch_simple(const SimpleArgs &a, hipStream_t st);
 
 // Split of f32 operands into bf16 planes for the BF16xN precisions.
-hipError_t launch_split_rows(const float *src, int64_t ld, int32_t rows,
-                             int32_t cols, int nplanes, const int8_t *order,
-                             void *dst, int64_t ldd, int64_t plane_stride,
-                             hipStream_t st);
+struct SplitArgs {
+    const float *src;      // rows x cols
+    uint16_t *dst;         // plane block b at b * plane_stride, rows ldd apart
+    int64_t ld, ldd, plane_stride;
+    int32_t rows, cols;
+    int32_t blocks;        // nplanes blocks, block b = plane order[b]
+    uint32_t order;        // four bits each
+};
+hipError_t launch_split(const SplitArgs &a, const SplitArgs &b,
+                        hipStream_t st);
 
 hipError_t launch_error_norm(const void *c, int c_bf16, const double *r,
                              int64_t n, double *out, hipStream_t st);

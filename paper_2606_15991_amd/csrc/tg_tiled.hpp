@@ -14,6 +14,7 @@ struct VariantEntry {
     const void *grouped;
     int threads;
     int smem;
+    const void *planes = nullptr;   // products of planes (GemmArgs::kp)
 };
 
 // The phased schedule's entries (gemm_phased.hip).

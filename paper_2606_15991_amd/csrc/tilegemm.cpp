@@ -1188,32 +1188,51 @@ tg_status tile_gemm(const tg_in *A, const tg_in *B, tg_out *C,
             return fail(TG_E_ALIAS, "workspace shares bytes with an operand");
         char *ws = static_cast<char *>(o->workspace);
         size_t a_bytes = ((size_t)p.M * p.K * np * 2 + 255) & ~(size_t)255;
-        void *ap = ws, *bp = ws + a_bytes;
-        const int8_t *oa = np == 3 ? kX3A : kX6A;
-        const int8_t *ob = np == 3 ? kX3B : kX6B;
-        int64_t Kc = p.K * np;
-        // A' = M x (np K): plane block b occupies columns [b K, (b+1) K)
-        e = launch_split_rows(static_cast<const float *>(A->data), A->ld,
-                              (int32_t)p.M, (int32_t)p.K, np, oa, ap, Kc,
-                              p.K, hs);
-        if (e != hipSuccess) return hip_fail(e, "split launch");
-        if (p.b_nk) {
-            // B stored N x K -> B' = N x (np K)
-            e = launch_split_rows(static_cast<const float *>(B->data), B->ld,
-                                  (int32_t)p.N, (int32_t)p.K, np, ob, bp, Kc,
-                                  p.K, hs);
-        } else {
-            // B stored K x N -> B' = (np K) x N: plane block b is rows
-            // [b K, (b+1) K)
-            e = launch_split_rows(static_cast<const float *>(B->data), B->ld,
-                                  (int32_t)p.K, (int32_t)p.N, np, ob, bp, p.N,
-                                  p.K * p.N, hs);
+        uint32_t oa = 0, ob = 0;
+        for (int b = 0; b < np; ++b) {
+            oa |= (uint32_t)(np == 3 ? kX3A : kX6A)[b] << (4 * b);
+            ob |= (uint32_t)(np == 3 ? kX3B : kX6B)[b] << (4 * b);
         }
+        // Where the kernel can step from plane to plane itself (whole K
+        // tiles in each) every plane is stored once, else once for each
+        // product that reads it.
+        const bool once = tiled_planes(L.variant) && p.K > 0 &&
+                          p.K % tiled_variant(L.variant).bk == 0;
+        if (once) {
+            g.kp = (int32_t)p.K;
+            g.planes_a = oa;
+            g.planes_b = ob;
+            oa = ob = 0x210;
+        }
+        const int blocks = once ? (np == 3 ? 2 : 3) : np;
+        const int64_t Kc = p.K * blocks;
+        // A' = M x (blocks K): plane block b occupies columns [b K, (b+1) K)
+        SplitArgs sa_{}, sb_{};
+        sa_.src = static_cast<const float *>(A->data);
+        sa_.ld = A->ld;
+        sa_.dst = reinterpret_cast<uint16_t *>(ws);
+        sa_.rows = (int32_t)p.M;
+        sa_.cols = (int32_t)p.K;
+        sa_.ldd = Kc;
+        sa_.plane_stride = p.K;
+        sa_.order = oa;
+        sa_.blocks = sb_.blocks = blocks;
+        sb_.src = static_cast<const float *>(B->data);
+        sb_.ld = B->ld;
+        sb_.dst = reinterpret_cast<uint16_t *>(ws + a_bytes);
+        sb_.order = ob;
+        // B stored N x K -> B' = N x (blocks K); stored K x N -> B' =
+        // (blocks K) x N: plane block b is rows [b K, (b+1) K)
+        sb_.rows = (int32_t)(p.b_nk ? p.N : p.K);
+        sb_.cols = (int32_t)(p.b_nk ? p.K : p.N);
+        sb_.ldd = p.b_nk ? Kc : p.N;
+        sb_.plane_stride = p.b_nk ? p.K : p.K * p.N;
+        e = launch_split(sa_, sb_, hs);
         if (e != hipSuccess) return hip_fail(e, "split launch");
-        g.a = ap; g.b = bp;
+        g.a = sa_.dst; g.b = sb_.dst;
         g.lda = Kc;
-        g.ldb = p.b_nk ? Kc : p.N;
-        g.K = (int32_t)Kc;
+        g.ldb = sb_.ldd;
+        g.K = (int32_t)(p.K * np);
     }
     e = launch_tiled(L.variant, g, hs);
     return e == hipSuccess ? TG_OK : hip_fail(e, "tiled kernel launch");
