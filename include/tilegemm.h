@@ -157,7 +157,9 @@ typedef struct tg_config {
     int32_t kind;         /* tg_kind                                         */
     int32_t bm, bn, bk;
     int32_t wm, wn;
-    int32_t ksplit;       /* skinny kernel: wavefronts sharing one tile's K  */
+    int32_t ksplit;       /* skinny kernel: wavefronts sharing one tile's K
+                             (unsplit products of many columns run eight
+                             wavefronts over several tiles instead)        */
     int32_t stages;       /* tiled kernel: LDS stages of the K-tile ring;
                              with TG_SCHED_CROSS, 3 means five slots of one
                              operand tile each (A or B of a K tile)         */

@@ -26,6 +26,7 @@
 #include "tg_device.hpp"
 #include "tg_elementwise.hpp"
 #include "tg_internal.hpp"
+#include "tg_tiled.hpp"
 
 namespace tg {
 namespace {
@@ -399,6 +400,222 @@ __global__ __launch_bounds__(256) void skinny_merge_kernel(SkinnyArgs g,
     }
 }
 
+// Streaming form of the unsplit product for outputs of many columns.  What
+// holds the plain form back is the load path: a fragment load touches 16
+// rows of 64 bytes, 64 cache-line lookups for 1 KiB, and each program of few
+// columns loads the activations anew, as many bytes as weights.  Here a
+// workgroup of eight wavefronts takes `q` consecutive programs, i.e. a run
+// of q bn columns in row tiles of 16 whatever bn is.  The wavefronts share
+// K, 128 bytes of every row in turn.  Weights go from memory to LDS by
+// direct loads of whole lines (8 rows of 128 bytes; the 16-byte chunk c of
+// row r at c ^ ((r >> 1) & 7), so that the fragment reads are free of bank
+// conflicts) into a ring of kStreamRing tiles per wavefront, which no other
+// wavefront reads: no barrier, and the next kStreamRing - 1 tiles in flight
+// throughout, over the end of a row tile too.  The activations stand in LDS
+// once.  At the end of a row tile the
+// wavefronts' partial tiles meet in LDS and are summed in their order.
+// Measured (cold weights): e4m3 (8, 51200, 5120) 55 us against 73, one row
+// 49.5 against 58; bf16 95 against 120 and 89 against 95; (1, 5120, 5120) e4m3
+// 9.6 against 10.3; reading 262 MB alone takes 45 us on this chip.
+constexpr int kStreamWaves = 8;
+constexpr int kStreamRing = 4;
+constexpr int kStreamTile = 16 * 128;                       // bytes
+constexpr int kStreamLds =    // ring, and two sets of partial tiles
+    kStreamWaves * (kStreamRing * kStreamTile + 2 * 1024);
+
+template <int WDT, bool CBF16>
+__global__ __launch_bounds__(kStreamWaves * 64) void skinny_stream_kernel(
+    SkinnyArgs g, int q) {
+    constexpr int WES = WDT == TG_BF16 ? 2 : 1, XV = WDT == TG_BF16 ? 1 : 2;
+    extern __shared__ __align__(1024) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char *ring = lds + wave * kStreamRing * kStreamTile;
+    float *part = reinterpret_cast<float *>(
+        lds + kStreamWaves * kStreamRing * kStreamTile);
+    char *xs = lds + kStreamLds;
+    const int r = lane & 15, grp = lane >> 4;
+    // this workgroup's columns
+    const int c0 = blockIdx.x * q * g.bn;
+    const int cols = min(g.N - c0, q * g.bn);
+    const int tiles = (cols + 15) / 16;
+    const int kbytes = g.K * WES, nkb = (kbytes + 127) / 128;
+    const uint32_t ldw = (uint32_t)(g.ldw * WES);
+    // rows past the columns lie past the buffer's end and load as zeros
+    const i32x4 W = make_srd(
+        static_cast<const char *>(g.w) + (int64_t)c0 * g.ldw * WES,
+        (uint32_t)cols * ldw);
+    // this lane's row and chunk of both loads of a tile
+    const int lrow = lane >> 3;
+    uint32_t lch[2], loff[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = i * 8 + lrow;
+        lch[i] = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+        loff[i] = row * ldw + lch[i];
+    }
+    // The wavefront's tiles in order: 128-byte blocks wave, wave + 8, ... of
+    // row tile 0, of row tile 1 and so on.
+    const int total =
+        tiles * ((nkb - wave + kStreamWaves - 1) / kStreamWaves);
+    int ikb = wave;               // block of the tile that is loaded next
+    uint32_t irow = 0;            // byte offset of its rows
+    auto issue = [&](int slot) {
+        char *dst = ring + slot * kStreamTile;
+        const uint32_t k = ikb * 128;
+        const bool whole = (ikb + 1) * 128 <= kbytes;
+        uint32_t v[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            v[i] = whole || (int)(k + lch[i]) < kbytes
+                       ? irow + loff[i] + k : kOutOfRange;
+        dma16<true>(W, dst, v[0]);
+        dma16<false>(W, dst + 1024, v[1]);
+        ikb += kStreamWaves;
+        if (ikb >= nkb) {
+            ikb = wave;
+            irow += 16 * ldw;
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kStreamRing; ++i)
+        if (i < total) issue(i);
+    // Activations: 16-byte chunk kc of row m at chunk kc ^ m of its row, rows
+    // of whole 256 bytes, zeros past K.  (Direct loads: all of them are in
+    // flight at once; through registers, row by row, 80 KiB took 9 us.)
+    const int rowc = (g.K + 127) / 128 * 16;     // chunks of a row
+    {
+        const i32x4 X = make_srd(g.x, (uint32_t)(g.M * g.ldx * 2));
+        for (int i = wave; i * 64 < g.M * rowc; i += kStreamWaves) {
+            const int e = i * 64 + lane, m = e / rowc;
+            const int kc = (e - m * rowc) ^ m;
+            dma16<true>(X, xs + i * 1024,
+                        m < g.M && kc * 8 < g.K
+                            ? (uint32_t)(m * g.ldx * 2 + kc * 16)
+                            : kOutOfRange);
+        }
+        wait_vmem();
+        __syncthreads();
+    }
+    const int wr0 = r * 128 + ((grp ^ ((r >> 1) & 7)) << 4);
+    const int wr1 = r * 128 + (((grp + 4) ^ ((r >> 1) & 7)) << 4);
+    // activation chunks of block kb: bf16 kb * 8 + 4 h + grp, e4m3 kb * 16 +
+    // 8 h + 2 grp + c; this wavefront's blocks are all even or all odd
+    const int xrow = r < g.M ? r : 0;
+    const char *xp[2 * XV];
+#pragma unroll
+    for (int c = 0; c < 2 * XV; ++c) {
+        const int kc = XV == 1 ? (wave & 1) * 8 + 4 * c + grp
+                               : 8 * (c >> 1) + 2 * grp + (c & 1);
+        xp[c] = xs + (xrow * rowc + (kc ^ xrow)) * 16;
+    }
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    int kb = wave, tile = 0;
+    for (int it = 0; it < total; ++it) {
+        if (total - 1 - it >= kStreamRing - 1)
+            wait_vmem_le<2 * (kStreamRing - 1)>();
+        else
+            wait_vmem();
+        asm volatile("" ::: "memory");
+        const int slot = it % kStreamRing;
+        const char *wt = ring + slot * kStreamTile;
+        const i32x4 w[2] = {*reinterpret_cast<const i32x4 *>(wt + wr0),
+                            *reinterpret_cast<const i32x4 *>(wt + wr1)};
+        i32x4 x[2 * XV];
+        const int xk = (XV == 1 ? kb >> 1 : kb) * 256;
+#pragma unroll
+        for (int c = 0; c < 2 * XV; ++c)
+            x[c] = *reinterpret_cast<const i32x4 *>(xp[c] + xk);
+        // the slot is free once its fragments are in registers
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (it + kStreamRing < total) issue(slot);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if constexpr (WDT == TG_BF16) {
+                acc = mfma16_bf16(w[h], x[h], acc);
+            } else {
+                const uint2 w0 = e4m3x4_to_bf16x4(w[h][0]);
+                const uint2 w1 = e4m3x4_to_bf16x4(w[h][1]);
+                const uint2 w2 = e4m3x4_to_bf16x4(w[h][2]);
+                const uint2 w3 = e4m3x4_to_bf16x4(w[h][3]);
+                acc = mfma16_bf16(i32x4{(int)w0.x, (int)w0.y, (int)w1.x,
+                                        (int)w1.y}, x[XV * h], acc);
+                acc = mfma16_bf16(i32x4{(int)w2.x, (int)w2.y, (int)w3.x,
+                                        (int)w3.y}, x[XV * h + XV - 1], acc);
+            }
+        }
+        kb += kStreamWaves;
+        if (kb < nkb) continue;
+        // The end of a row tile.  The set of partial tiles written now was
+        // last read before the barrier of the row tile before.
+        kb = wave;
+        float *set = part + (tile & 1) * kStreamWaves * 256;
+        reinterpret_cast<f32x4 *>(set)[wave * 64 + lane] = acc;
+        acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        // four wavefronts in turn: thread e: lane e / 4, register e % 4 of
+        // the result layout (lane l, register v: weight row 4 (l / 16) + v,
+        // output row l % 16)
+        const int m = (tid >> 2) & 15, e = tid & 255;
+        const int c = tile * 16 + 4 * (e >> 6) + (e & 3);
+        if ((wave >> 2) == (tile & 1) && m < g.M && c < cols) {
+            float s = set[e];
+#pragma unroll
+            for (int w = 1; w < kStreamWaves; ++w) s += set[w * 256 + e];
+            const int n = c0 + c;
+            float y = s * (g.scale_a ? g.scale_a[m] : 1.0f);
+            if (g.scale_w) y *= g.scale_w[n];
+            if (g.res) y += residual_at(g, m, n);
+            const int64_t off = (int64_t)m * g.ldy + n;
+            if constexpr (CBF16)
+                static_cast<uint16_t *>(g.y)[off] = f32_to_bf16_bits(y);
+            else
+                static_cast<float *>(g.y)[off] = y;
+            if (g.wcount) atomicAdd(&g.wcount[(int64_t)m * g.N + n], 1);
+        }
+        ++tile;
+    }
+}
+
+// Bytes of LDS of the streaming form, or 0 where it cannot run the product:
+// K of whole 16-byte weight chunks, a block of K for every wavefront, the
+// activations within LDS.
+int64_t stream_lds(int w_dtype, const SkinnyArgs &a) {
+    const int wes = w_dtype == TG_BF16 ? 2 : 1;
+    const int64_t kbytes = (int64_t)a.K * wes;
+    const int64_t nkb = (kbytes + 127) / 128;
+    if (a.splitk > 1 || kbytes % 16 || kbytes > 0x7fffffff ||
+        nkb < kStreamWaves)
+        return 0;
+    const int64_t x = ((int64_t)a.K + 127) / 128 * 256 * a.M;
+    const int64_t lds = kStreamLds + (x + 1023) / 1024 * 1024;
+    return lds <= 160 * 1024 && a.M * a.ldx * 2 < 0x7fffffff ? lds : 0;
+}
+
+// Whether the streaming form is the faster one.  Its workgroups are dealt
+// whole programs, so the last ones may get none: from 85 in 100 workgroups'
+// worth of programs on it is ahead (cold e4m3 weights, one row: (25600, 5120)
+// in 16-column programs, 89 in 100, 28.4 us against 34.9, but (10240, 5120),
+// 83, 18.7 against 17.7 and (12800, 5120), 78, 21.8 against 21.0).  And a row
+// tile ends in a barrier, which needs twelve blocks of K to be hidden: e4m3
+// (4, 51200, 1024), eight, 19.7 us against 16.8, (4, 30000, 1536) 15.5
+// against 16.3.
+bool stream_pays(int64_t kbytes, int64_t progs, int64_t groups, int64_t q) {
+    return kbytes > 11 * 128 && 20 * progs >= 17 * q * groups;
+}
+
+template <int WDT, bool CBF16>
+hipError_t launch_stream(const SkinnyArgs &a, int q, int grid, size_t lds,
+                         hipStream_t st) {
+    static const hipError_t ready = hipFuncSetAttribute(
+        reinterpret_cast<const void *>(&skinny_stream_kernel<WDT, CBF16>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (ready != hipSuccess) return ready;
+    hipLaunchKernelGGL((skinny_stream_kernel<WDT, CBF16>), dim3(grid),
+                       dim3(kStreamWaves * 64), lds, st, a, q);
+    return hipGetLastError();
+}
+
 template <int WDT, int KS, int RT>
 hipError_t launch_ks(int c_bf16, const SkinnyArgs &a, hipStream_t st) {
     dim3 grid((a.N + a.bn - 1) / a.bn, a.splitk), block(KS * 64);
@@ -503,7 +720,31 @@ hipError_t launch_skinny_norm(int w_dtype, int c_bf16, int bn, int ksplit,
 }
 
 hipError_t launch_skinny(int w_dtype, int c_bf16, int bn, int ksplit,
-                         const SkinnyArgs &a, hipStream_t st) {
+                         const SkinnyArgs &a, int cus, hipStream_t st) {
+    const int64_t lds = bn == a.bn ? stream_lds(w_dtype, a) : 0;
+    if (lds) {
+        // one workgroup per compute unit
+        const int64_t progs = (a.N + (int64_t)bn - 1) / bn;
+        const int64_t groups = cus > 0 ? cus : 256;
+        const int64_t q = (progs + groups - 1) / groups;
+        const int grid = (int)((progs + q - 1) / q);
+        const int64_t span =
+            (q * bn + 16) * a.ldw * (w_dtype == TG_BF16 ? 2 : 1);
+        if (span < 0x7fffffff &&
+            stream_pays(w_dtype == TG_BF16 ? a.K * (int64_t)2 : a.K, progs,
+                        groups, q)) {
+            if (w_dtype == TG_BF16)
+                return c_bf16
+                           ? launch_stream<TG_BF16, true>(a, (int)q, grid,
+                                                          lds, st)
+                           : launch_stream<TG_BF16, false>(a, (int)q, grid,
+                                                           lds, st);
+            return c_bf16 ? launch_stream<TG_FP8_E4M3, true>(a, (int)q, grid,
+                                                             lds, st)
+                          : launch_stream<TG_FP8_E4M3, false>(a, (int)q,
+                                                              grid, lds, st);
+        }
+    }
     if (w_dtype == TG_BF16)
         return launch_bn<TG_BF16>(c_bf16, bn, ksplit, a, st);
     if (w_dtype == TG_FP8_E4M3)

@@ -144,7 +144,7 @@ struct SkinnyArgs {
     int32_t res_bf16;
 };
 hipError_t launch_skinny(int w_dtype, int c_bf16, int bn, int ksplit,
-                         const SkinnyArgs &a, hipStream_t st);
+                         const SkinnyArgs &a, int cus, hipStream_t st);
 // Merge of a split decode product: one program per bm x bn sub-tensor of
 // y sums the splitk partial tiles in split order, applies the scales (and
 // the fused normalisation's row scale when norm is set) and stores y.

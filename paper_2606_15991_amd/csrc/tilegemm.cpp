@@ -469,6 +469,10 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
         // the decode defaults assume MI355X's 256 compute units where the
         // device cannot be asked (host-only planning)
         const int64_t ncu = cus > 0 ? cus : 256;
+        // (The rules below were measured on the plain form of the kernel.
+        // Where the streaming form runs instead, their programs' columns are
+        // dealt to one workgroup per compute unit and ksplit is not used;
+        // the even widths suit it too.)
         // One round of programs, one per compute unit: where N / ncu is 8 to
         // 32 columns, programs of that many columns fill the machine with
         // no K split and so no merge launch.  Measured on (M, N, K) =
@@ -1145,7 +1149,8 @@ tg_status tile_gemm(const tg_in *A, const tg_in *B, tg_out *C,
                 return st;
             a.part = static_cast<float *>(o->workspace);
         }
-        e = launch_skinny(p.b_dt, p.c_bf16, L.cfg.bn, L.cfg.ksplit, a, hs);
+        e = launch_skinny(p.b_dt, p.c_bf16, L.cfg.bn, L.cfg.ksplit, a,
+                          device_cus(), hs);
         if (e == hipSuccess && a.splitk > 1)
             e = launch_skinny_merge(p.c_bf16, a, false, 0.f, hs);
         return e == hipSuccess ? TG_OK : hip_fail(e, "decode kernel launch");
