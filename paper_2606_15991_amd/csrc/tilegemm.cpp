@@ -1384,7 +1384,8 @@ tg_status tile_gemm_grouped_prepare(int32_t n, const tg_in *A,
         C[i].bn = cfg.bn;
     }
     // longest K first: programs take tiles in table order with a fixed
-    // stride, so the costliest tiles are spread over all programs first
+    // stride (every other row of them backwards), so the costliest tiles are
+    // spread over all programs first
     std::vector<int32_t> order((size_t)n);
     for (int32_t i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
