@@ -486,7 +486,8 @@ typedef struct tg_tune_result {
 /*
  * tile_autotune -- run every candidate once (warm-up) then `reps` times on
  * `stream`, timed with HIP events, and record the fastest in the tuning
- * cache.  C is written (any candidate's result).  results (host, up to
+ * cache.  From four launches on they are dealt over two to four passes over
+ * the candidates (a warm-up in each) and the fastest pass's average counts.  C is written (any candidate's result).  results (host, up to
  * max_results entries) and best (host) may be NULL.  Synchronises the
  * stream: not capturable.
  */
