@@ -119,6 +119,188 @@ __device__ __forceinline__ void ph_dma2(const i32x4 &srd, uint32_t base,
         : "memory", "scc");
 }
 
+// One such load.
+template <int OFF>
+__device__ __forceinline__ void ph_dma1(const i32x4 &srd, uint32_t base,
+                                        uint32_t v, int soff) {
+    asm volatile(
+        "s_add_u32 m0, %0, %4\n\ts_nop 3\n\t"
+        "buffer_load_dwordx4 %1, %2, %3 offen lds"
+        :
+        : "s"(base), "v"(v), "s"(srd),
+          "s"(__builtin_amdgcn_readfirstlane(soff)), "i"(OFF)
+        : "memory", "scc");
+}
+
+__device__ __forceinline__ int ph_swz(int row) { return (row >> 1) & 7; }
+
+// Wavefronts of TM x 64 outputs, as 16 x 16 blocks.
+template <class C>
+struct PhStore {
+    static_assert(C::TN == 64, "four column blocks a wavefront");
+    static constexpr int NRB = C::TM / 16;
+    typedef f32x4 Acc[NRB][4];
+
+    // Store the accumulators into the owned sub-tensor.  Result layout of
+    // the transposed 16 x 16 product: lane l, register v holds row l % 16,
+    // column 4 (l / 16) + v.  Stores coalesce over consecutive lanes only, so
+    // each wavefront passes blocks of 16 rows by 128 bytes (binary32 32
+    // columns, bf16 64) through 2 KiB of LDS of its own and stores eight
+    // rows of eight lanes by 16 bytes (256 KiB of one sub-tensor alone on
+    // the chip: 8300 cycles in the registers' order, 5600 in this one).
+    // A lane's 16 bytes that straddle N go out element by element; rows past
+    // M and columns past N get an out-of-range offset, which the hardware
+    // drops.  The accumulators are read by ordered assembly: left to itself
+    // the compiler copies all 128 at once and spills.
+    template <bool SCALED>
+    __device__ __forceinline__ static void store(const Job &j, Acc &acc,
+                                                 const char *scl, char *smem,
+                                                 int lane, int wave) {
+        const int wm = wave / C::WN, wn = wave % C::WN;
+        constexpr int OES = C::CBF16 ? 2 : 4, VW = 16 / OES;
+        int lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)j.ldc);
+        int hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(j.ldc >> 32));
+        // (formed here, not held across the K loop)
+        asm volatile("" : "+s"(lo), "+s"(hi));
+        const int64_t ldc =
+            (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+        char *base = static_cast<char *>(j.c) +
+                     ((int64_t)j.m0 * ldc + j.n0) * OES;
+        const __amdgpu_buffer_rsrc_t r = make_rsrc(
+            base, sat_bytes(((int64_t)(j.M - j.m0 - 1) * ldc +
+                             (j.N - j.n0)) * OES));
+        // this lane's place in a stored block: rows sr and sr + 8, bytes
+        // 16 sc
+        const int sr = lane >> 3, sc = lane & 7;
+        const int r0 = wm * C::TM + sr, c0 = wn * 64 + sc * VW;
+        const int rows_left = j.M - j.m0 - r0, cols_left = j.N - j.n0 - c0;
+        // and in a block of results: row ar, 16-byte chunks ag and ag + 4
+        const int ar = lane & 15, ag = lane >> 4;
+        const uint32_t blk = lds_addr(smem) + C::NS * C::STAGE +
+                             C::NSLOT * C::SCALE_SLOT + wave * 2048;
+        const uint32_t w0 = blk + ar * 128 + ((ag ^ ph_swz(ar)) << 4);
+        const uint32_t w1 = blk + ar * 128 + (((ag + 4) ^ ph_swz(ar)) << 4);
+        const uint32_t s0 = blk + sr * 128 + ((sc ^ ph_swz(sr)) << 4);
+        const uint32_t s1 = blk + (sr + 8) * 128 + ((sc ^ ph_swz(sr + 8)) << 4);
+        // bf16 rows that start inside a dword
+        const bool split = C::CBF16 &&
+                           (((reinterpret_cast<uintptr_t>(base) >> 1) |
+                             (uintptr_t)ldc) & 1);
+        // whole sub-tensors: no per-store tests
+        const bool inner = j.n0 + C::BN <= j.N && j.m0 + C::BM <= j.M &&
+                           !split;
+        const bool ragged = j.n0 + C::BN > j.N && j.N % VW != 0;
+        const float *lsa = reinterpret_cast<const float *>(scl);
+        const float *lsb = lsa + C::BM;
+        float sb[SCALED ? 16 : 1];
+        if constexpr (SCALED) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                // column of register e % 4 of fragment e / 4
+                const int c = wn * 64 +
+                              (C::CBF16 ? (e >> 3) * 32 + 8 * ag + (e & 7)
+                                        : (e >> 2) * 16 + 4 * ag + (e & 3));
+                sb[e] = j.scale_b ? lsb[c] : 1.f;
+            }
+        }
+        const uint32_t off0 = (uint32_t)((r0 * ldc + c0) * OES);
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) {
+            float sa = 1.f;
+            if constexpr (SCALED)
+                if (j.scale_a) sa = lsa[wm * C::TM + i * 16 + ar];
+#pragma unroll
+            for (int h = 0; h < 8 / VW; ++h) {   // 2, bf16 1
+                // VW / 2 fragments of this block: two chunks a lane
+                float x[2 * VW];
+#pragma unroll
+                for (int v = 0; v < 2 * VW; ++v) {
+                    const int e = h * 2 * VW + v;
+                    const float a = acc[i][e >> 2][e & 3];
+#ifdef __HIP_DEVICE_COMPILE__
+                    asm volatile("v_accvgpr_read_b32 %0, %1"
+                                 : "=v"(x[v]) : "a"(a));
+#endif
+                    if constexpr (SCALED) x[v] = x[v] * sb[e] * sa;
+                }
+                u32x4 wa, wb;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if constexpr (C::CBF16) {
+                        wa[q] = f32x2_to_bf16x2(x[2 * q], x[2 * q + 1]);
+                        wb[q] = f32x2_to_bf16x2(x[VW + 2 * q],
+                                                x[VW + 2 * q + 1]);
+                    } else {
+                        wa[q] = as_u32(x[q]);
+                        wb[q] = as_u32(x[VW + q]);
+                    }
+                }
+                // (a wavefront's LDS accesses execute in order)
+                *reinterpret_cast<lds_u32x4 *>(w0) = wa;
+                *reinterpret_cast<lds_u32x4 *>(w1) = wb;
+                __builtin_amdgcn_wave_barrier();
+                const u32x4 ya = *reinterpret_cast<const lds_u32x4 *>(s0);
+                const u32x4 yb = *reinterpret_cast<const lds_u32x4 *>(s1);
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t off = off0 + (uint32_t)(i * 16 * ldc * OES) +
+                                     h * 128;
+                const uint32_t off8 = off + (uint32_t)(8 * ldc * OES);
+                if (inner) {
+                    __builtin_amdgcn_raw_buffer_store_b128(ya, r, off, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(yb, r, off8, 0, 0);
+                } else {
+                    const int cl = cols_left - h * 32;
+                    put_edge<VW>(r, base, ya, off, i * 16 < rows_left, cl,
+                                 split, ragged);
+                    put_edge<VW>(r, base, yb, off8, i * 16 + 8 < rows_left,
+                                 cl, split, ragged);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (j.wcount) {
+            // instrumented launches: one count per stored element
+#pragma unroll 1
+            for (int i = 0; i < 2 * NRB; ++i) {
+                if (i * 8 >= rows_left) continue;
+#pragma unroll 1
+                for (int e = 0; e < 8; ++e) {
+                    const int c = (e / VW) * 32 + e % VW;
+                    if (c < cols_left)
+                        atomicAdd(&j.wcount[(int64_t)(j.m0 + r0 + i * 8) *
+                                                j.N + j.n0 + c0 + c], 1);
+                }
+            }
+        }
+    }
+    // 16 bytes at an edge of the output: cl columns of it are left.
+    template <int VW>
+    __device__ __forceinline__ static void put_edge(
+        const __amdgpu_buffer_rsrc_t &r, char *base, const u32x4 &w,
+        uint32_t off, bool row_in, int cl, bool split, bool ragged) {
+        const bool in = row_in && cl >= VW;
+        if (!split)
+            __builtin_amdgcn_raw_buffer_store_b128(
+                w, r, in ? off : kOutOfRange, 0, 0);
+        else if (in)
+            __builtin_memcpy(base + off, &w, 16);
+        if (ragged) {
+#pragma unroll
+            for (int v = 0; v < VW - 1; ++v) {
+                const uint32_t o = row_in && !in && v < cl
+                                       ? off + v * (16 / VW) : kOutOfRange;
+                if constexpr (VW == 8)
+                    __builtin_amdgcn_raw_buffer_store_b16(
+                        (unsigned short)(w[v >> 1] >> (16 * (v & 1))), r, o,
+                        0, 0);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b32(w[v & 3], r, o, 0,
+                                                          0);
+            }
+        }
+    }
+};
+
 // PL: the operands are planes of a split binary32 product, side by side
 // along K (K % 64 == 0 elements each), and the K loop runs over products of
 // planes: block b of kp elements multiplies plane a of A and plane b of B as
@@ -136,7 +318,8 @@ struct Phased {
     using FA = PhFrag<C, 4>;      // half of A's rows of a wavefront
     using FB = PhFrag<C, 2>;      // half of B's columns
     static constexpr int NQ = FA::NQ;
-    typedef f32x4 Acc[8][4];      // 16 x 16 blocks of 128 x 64 outputs
+    typedef PhStore<C> Store;
+    typedef typename Store::Acc Acc;
 
     // LDS stage: A half 0, A half 1, B half 0, B half 1, each 128 rows of
     // 128 bytes with 16-byte chunk c of row r at c ^ ((r >> 1) & 7) (k-major
@@ -174,7 +357,7 @@ struct Phased {
                                : p;
         return (lr >> 5) * 64 + h * 32 + n;
     }
-    __device__ __forceinline__ static int swz7(int lr) { return (lr >> 1) & 7; }
+    __device__ __forceinline__ static int swz7(int lr) { return ph_swz(lr); }
 
     __device__ __forceinline__ void init(char *s) {
         smem = s;
@@ -491,162 +674,6 @@ struct Phased {
         slots<1, 0>(a, x, acc);
     }
 
-    // Store the accumulators into the owned sub-tensor.  Result layout of
-    // the transposed 16 x 16 product: lane l, register v holds row l % 16,
-    // column 4 (l / 16) + v.  Stores coalesce over consecutive lanes only, so
-    // each wavefront passes blocks of 16 rows by 128 bytes (binary32 32
-    // columns, bf16 64) through 2 KiB of LDS of its own and stores eight
-    // rows of eight lanes by 16 bytes (256 KiB of one sub-tensor alone on
-    // the chip: 8300 cycles in the registers' order, 5600 in this one).
-    // A lane's 16 bytes that straddle N go out element by element; rows past
-    // M and columns past N get an out-of-range offset, which the hardware
-    // drops.  The accumulators are read by ordered assembly: left to itself
-    // the compiler copies all 128 at once and spills.
-    template <bool SCALED>
-    __device__ __forceinline__ void store(const Job &j, Acc &acc,
-                                          const char *scl) const {
-        constexpr int OES = C::CBF16 ? 2 : 4, VW = 16 / OES;
-        int lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)j.ldc);
-        int hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(j.ldc >> 32));
-        // (formed here, not held across the K loop)
-        asm volatile("" : "+s"(lo), "+s"(hi));
-        const int64_t ldc =
-            (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-        char *base = static_cast<char *>(j.c) +
-                     ((int64_t)j.m0 * ldc + j.n0) * OES;
-        const __amdgpu_buffer_rsrc_t r = make_rsrc(
-            base, sat_bytes(((int64_t)(j.M - j.m0 - 1) * ldc +
-                             (j.N - j.n0)) * OES));
-        // this lane's place in a stored block: rows sr and sr + 8, bytes
-        // 16 sc
-        const int sr = lane >> 3, sc = lane & 7;
-        const int r0 = wm * 128 + sr, c0 = wn * 64 + sc * VW;
-        const int rows_left = j.M - j.m0 - r0, cols_left = j.N - j.n0 - c0;
-        // and in a block of results: row ar, 16-byte chunks ag and ag + 4
-        const int ar = lane & 15, ag = lane >> 4;
-        const uint32_t blk = lds_addr(smem) + 2 * C::STAGE +
-                             C::NSLOT * C::SCALE_SLOT + wave * 2048;
-        const uint32_t w0 = blk + ar * 128 + ((ag ^ swz7(ar)) << 4);
-        const uint32_t w1 = blk + ar * 128 + (((ag + 4) ^ swz7(ar)) << 4);
-        const uint32_t s0 = blk + sr * 128 + ((sc ^ swz7(sr)) << 4);
-        const uint32_t s1 = blk + (sr + 8) * 128 + ((sc ^ swz7(sr + 8)) << 4);
-        // bf16 rows that start inside a dword
-        const bool split = C::CBF16 &&
-                           (((reinterpret_cast<uintptr_t>(base) >> 1) |
-                             (uintptr_t)ldc) & 1);
-        // whole sub-tensors: no per-store tests
-        const bool inner = j.n0 + 256 <= j.N && j.m0 + 256 <= j.M && !split;
-        const bool ragged = j.n0 + 256 > j.N && j.N % VW != 0;
-        const float *lsa = reinterpret_cast<const float *>(scl);
-        const float *lsb = lsa + 256;
-        float sb[SCALED ? 16 : 1];
-        if constexpr (SCALED) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                // column of register e % 4 of fragment e / 4
-                const int c = wn * 64 +
-                              (C::CBF16 ? (e >> 3) * 32 + 8 * ag + (e & 7)
-                                        : (e >> 2) * 16 + 4 * ag + (e & 3));
-                sb[e] = j.scale_b ? lsb[c] : 1.f;
-            }
-        }
-        const uint32_t off0 = (uint32_t)((r0 * ldc + c0) * OES);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float sa = 1.f;
-            if constexpr (SCALED)
-                if (j.scale_a) sa = lsa[wm * 128 + i * 16 + ar];
-#pragma unroll
-            for (int h = 0; h < 8 / VW; ++h) {   // 2, bf16 1
-                // VW / 2 fragments of this block: two chunks a lane
-                float x[2 * VW];
-#pragma unroll
-                for (int v = 0; v < 2 * VW; ++v) {
-                    const int e = h * 2 * VW + v;
-                    const float a = acc[i][e >> 2][e & 3];
-#ifdef __HIP_DEVICE_COMPILE__
-                    asm volatile("v_accvgpr_read_b32 %0, %1"
-                                 : "=v"(x[v]) : "a"(a));
-#endif
-                    if constexpr (SCALED) x[v] = x[v] * sb[e] * sa;
-                }
-                u32x4 wa, wb;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if constexpr (C::CBF16) {
-                        wa[q] = f32x2_to_bf16x2(x[2 * q], x[2 * q + 1]);
-                        wb[q] = f32x2_to_bf16x2(x[VW + 2 * q],
-                                                x[VW + 2 * q + 1]);
-                    } else {
-                        wa[q] = as_u32(x[q]);
-                        wb[q] = as_u32(x[VW + q]);
-                    }
-                }
-                // (a wavefront's LDS accesses execute in order)
-                *reinterpret_cast<lds_u32x4 *>(w0) = wa;
-                *reinterpret_cast<lds_u32x4 *>(w1) = wb;
-                __builtin_amdgcn_wave_barrier();
-                const u32x4 ya = *reinterpret_cast<const lds_u32x4 *>(s0);
-                const u32x4 yb = *reinterpret_cast<const lds_u32x4 *>(s1);
-                __builtin_amdgcn_wave_barrier();
-                const uint32_t off = off0 + (uint32_t)(i * 16 * ldc * OES) +
-                                     h * 128;
-                const uint32_t off8 = off + (uint32_t)(8 * ldc * OES);
-                if (inner) {
-                    __builtin_amdgcn_raw_buffer_store_b128(ya, r, off, 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(yb, r, off8, 0, 0);
-                } else {
-                    const int cl = cols_left - h * 32;
-                    put_edge<VW>(r, base, ya, off, i * 16 < rows_left, cl,
-                                 split, ragged);
-                    put_edge<VW>(r, base, yb, off8, i * 16 + 8 < rows_left,
-                                 cl, split, ragged);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        if (j.wcount) {
-            // instrumented launches: one count per stored element
-#pragma unroll 1
-            for (int i = 0; i < 16; ++i) {
-                if (i * 8 >= rows_left) continue;
-#pragma unroll 1
-                for (int e = 0; e < 8; ++e) {
-                    const int c = (e / VW) * 32 + e % VW;
-                    if (c < cols_left)
-                        atomicAdd(&j.wcount[(int64_t)(j.m0 + r0 + i * 8) *
-                                                j.N + j.n0 + c0 + c], 1);
-                }
-            }
-        }
-    }
-    // 16 bytes at an edge of the output: cl columns of it are left.
-    template <int VW>
-    __device__ __forceinline__ static void put_edge(
-        const __amdgpu_buffer_rsrc_t &r, char *base, const u32x4 &w,
-        uint32_t off, bool row_in, int cl, bool split, bool ragged) {
-        const bool in = row_in && cl >= VW;
-        if (!split)
-            __builtin_amdgcn_raw_buffer_store_b128(
-                w, r, in ? off : kOutOfRange, 0, 0);
-        else if (in)
-            __builtin_memcpy(base + off, &w, 16);
-        if (ragged) {
-#pragma unroll
-            for (int v = 0; v < VW - 1; ++v) {
-                const uint32_t o = row_in && !in && v < cl
-                                       ? off + v * (16 / VW) : kOutOfRange;
-                if constexpr (VW == 8)
-                    __builtin_amdgcn_raw_buffer_store_b16(
-                        (unsigned short)(w[v >> 1] >> (16 * (v & 1))), r, o,
-                        0, 0);
-                else
-                    __builtin_amdgcn_raw_buffer_store_b32(w[v & 3], r, o, 0,
-                                                          0);
-            }
-        }
-    }
-
     template <class P>
     __device__ __forceinline__ void start_offsets(const P &prov) {
         if constexpr (PL) {
@@ -706,9 +733,12 @@ struct Phased {
                 issue_first();
             }
             if (done.scale_a || done.scale_b)
-                store<true>(done, acc, scale_slot<C>(smem, njob));
+                Store::template store<true>(done, acc,
+                                            scale_slot<C>(smem, njob), smem,
+                                            lane, wave);
             else
-                store<false>(done, acc, nullptr);
+                Store::template store<false>(done, acc, nullptr, smem, lane,
+                                             wave);
             if (!more) break;
             ++njob;
         }
@@ -733,6 +763,378 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_phased_grouped_kernel(
     GroupProvider<C> p{tab, n, total, G};
     Phased<C> k;
     k.run(p, smem);
+}
+
+// 128 x 128 sub-tensors: the same two groups of wavefronts one slot apart
+// (wavefronts 4 - 7, rows 64 .. 127, behind), but a wavefront's 32 x 64
+// outputs take only 48 registers of fragments for a whole K tile, so there
+// is one memory slot and one compute slot of 16 instructions per K tile, and
+// LDS holds four stages of which three are loaded ahead.  Bound by the memory
+// slot, 12 fragment reads and A's two loads of a wavefront; B's two loads in
+// front of the compute slot's instructions even the slots out (512 x 5120 x
+// 5120 37.6 us, all four in the memory slot 44.9).  Against eight wavefronts
+// in step with the same ring: 512 x 5120 x 5120 52.8 us, 2048^3 21.0 against
+// 25.3, e4m3 13.4 against 15.5.  Not for a k-major B, whose 16 transposing
+// reads make the memory slot longer (52 us against 50).
+//
+// MIX: bf16 A with e4m3 weights stored N x K (rows of 64 bytes in LDS, chunk
+// c of row r at c ^ ((r >> 2) & 3)), decoded to bf16 in the memory slot.  A
+// lane then holds 16 consecutive k of a weight row, eight for each K step,
+// and reads A's fragments at the same k.
+template <class C, bool MIX = false>
+struct Phased128 {
+    static_assert(C::BM == 128 && C::BN == 128 && C::RBY == 128 &&
+                      C::NW == 8 && C::WM == 4 && C::WN == 2 && C::NS == 4,
+                  "128 x 128 tiles, 4 x 2 wavefronts of 32 x 64");
+    static_assert(!C::B_KMAJOR && (!MIX || C::DTYPE == TG_BF16),
+                  "B stored N x K; bf16 by e4m3");
+    static constexpr int ABYTES = 128 * 128;
+    static constexpr int BROW = MIX ? 64 : 128;
+    static constexpr int STG = ABYTES + 128 * BROW;
+    static constexpr int LOADS = MIX ? 3 : 4;         // of a wavefront
+    static constexpr int SMEM =
+        C::NS * C::STAGE + C::NSLOT * C::SCALE_SLOT + 8 * 2048;
+    static_assert(SMEM <= 163840, "160 KiB of LDS");
+    static constexpr int BES = MIX ? 1 : C::ES;       // bytes of B's elements
+    using FA = PhFrag<C, 2>;
+    using FB = PhFrag<C, 4>;
+    static constexpr int NQ = FA::NQ;
+    typedef PhStore<C> Store;
+    typedef typename Store::Acc Acc;
+
+    char *smem;
+    int tid, lane, wave, wm, wn;
+    uint32_t aoff[2], boff[2], lbase;
+    Job j;
+    i32x4 sa, sb;
+    uint32_t va[2], vb[2];
+    int nk, head;
+
+    // a partial last K tile comes first
+    __device__ __forceinline__ int k0_of(int q) const {
+        return (head ? (q == 0 ? nk - 1 : q - 1) : q) * C::BK;
+    }
+    // column of LDS row lr of B (bf16 output: a lane's two fragments of 32
+    // columns hold eight consecutive ones)
+    __device__ __forceinline__ static int b_col(int lr) {
+        const int p = lr & 31;
+        return (lr & ~31) +
+               (C::CBF16 ? 8 * ((p >> 2) & 3) + 4 * (p >> 4) + (p & 3) : p);
+    }
+    __device__ __forceinline__ void init(char *s) {
+        smem = s;
+        tid = threadIdx.x;
+        lane = tid & 63;
+        wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        lbase = lds_addr(s) + wave * 1024;
+        wm = wave >> 1;
+        wn = wave & 1;
+        const int r = lane & 15, grp = lane >> 4;
+        const uint32_t base = lds_addr(s);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int ch = FA::F8 || MIX ? 2 * grp + q : 4 * q + grp;
+            const int c = (ch ^ ph_swz(r)) << 4;
+            aoff[q] = base + (wm * 32 + r) * 128 + c;
+            boff[q] = base + ABYTES + (wn * 64 + r) * 128 + c;
+        }
+        if constexpr (MIX)
+            boff[0] = base + ABYTES + (wn * 64 + r) * 64 +
+                      ((grp ^ ((r >> 2) & 3)) << 4);
+    }
+    // row and 16-byte chunk of K that lane l loads in 1 KiB block `blk`
+    __device__ __forceinline__ int a_row(int i) const {
+        return (i * 8 + wave) * 8 + (lane >> 3);
+    }
+    __device__ __forceinline__ int a_chunk(int i) const {
+        return (lane & 7) ^ ph_swz(a_row(i));
+    }
+    __device__ __forceinline__ int mb_row() const {       // MIX: B
+        return wave * 16 + (lane >> 2);
+    }
+    __device__ __forceinline__ int mb_chunk() const {
+        return (lane & 3) ^ ((mb_row() >> 2) & 3);
+    }
+    __device__ __forceinline__ void set_job(const Job &nj) {
+        j = nj;
+        j.K = __builtin_amdgcn_readfirstlane(j.K);
+        nk = (j.K + C::BK - 1) / C::BK;
+        head = j.K % C::BK ? 1 : 0;
+        sa = make_srd(j.a_row, sat_bytes(j.a_rem));
+        sb = make_srd(j.b_row, sat_bytes(j.b_rem));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            va[i] = (uint32_t)((a_row(i) * j.lda + a_chunk(i) * C::EPC) *
+                               C::ES);
+            if constexpr (MIX) {
+                vb[i] = (uint32_t)(b_col(mb_row()) * j.ldb + mb_chunk() * 16);
+            } else {
+                vb[i] = (uint32_t)((b_col(a_row(i)) * j.ldb +
+                                    a_chunk(i) * C::EPC) * C::ES);
+            }
+        }
+    }
+    __device__ __forceinline__ void load_b(uint32_t stage,
+                                           const uint32_t (&v)[2], int so) {
+        if constexpr (MIX)
+            ph_dma1<ABYTES>(sb, lbase + stage, v[0], so);
+        else
+            ph_dma2<ABYTES>(sb, lbase + stage, v, so);
+    }
+    // A's and B's share of sequence tile q into its stage.  In tile 0,
+    // possibly K's tail, chunks not wholly inside K load as zeros.
+    __device__ __forceinline__ void issue_a(int q) {
+        ph_dma2<0>(sa, lbase + (q & 3) * STG, va, k0_of(q) * C::ES);
+    }
+    __device__ __forceinline__ void issue_b(int q) {
+        load_b((q & 3) * STG, vb, k0_of(q) * BES);
+    }
+    __device__ __forceinline__ void issue_tile0() {
+        const int k0 = k0_of(0);
+        uint32_t w[2], u[2] = {vb[0], vb[1]};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bool in = k0 + (a_chunk(i) + 1) * C::EPC <= j.K;
+            w[i] = in ? va[i] : kOutOfRange;
+            if constexpr (!MIX)
+                u[i] = in ? vb[i] : kOutOfRange;
+        }
+        if constexpr (MIX)
+            if (k0 + (mb_chunk() + 1) * 16 > j.K) u[0] = kOutOfRange;
+        ph_dma2<0>(sa, lbase, w, k0 * C::ES);
+        load_b(0, u, k0 * BES);
+    }
+    __device__ __forceinline__ void issue_first() {
+        if (nk > 0) issue_tile0();
+#pragma unroll
+        for (int q = 1; q < 3; ++q)
+            if (q < nk) {
+                issue_a(q);
+                issue_b(q);
+            }
+    }
+    // The chunk that straddles K was loaded as zeros: its K % EPC valid
+    // elements of every row, one by one (MIX: K is whole chunks of both).
+    __device__ __forceinline__ void fill_tail() {
+        const int rem = j.K % C::EPC, kbase = j.K - rem;
+        const int chunk = (kbase - k0_of(0)) / C::EPC;
+        auto put = [&](char *dst, const char *src, bool ok) {
+            for (int e = 0; e < rem * C::ES; ++e) dst[e] = ok ? src[e] : 0;
+        };
+        for (int lr = tid; lr < 128; lr += C::THREADS)
+            put(smem + lr * 128 + ((chunk ^ ph_swz(lr)) << 4),
+                j.a + ((int64_t)(j.m0 + lr) * j.lda + kbase) * C::ES,
+                j.m0 + lr < j.M);
+        for (int lr = tid; lr < 128; lr += C::THREADS)
+            put(smem + ABYTES + lr * 128 + ((chunk ^ ph_swz(lr)) << 4),
+                j.b + ((int64_t)(j.n0 + b_col(lr)) * j.ldb + kbase) * C::ES,
+                j.n0 + b_col(lr) < j.N);
+    }
+    __device__ __forceinline__ static i32x4 ld(uint32_t p) {
+        return *reinterpret_cast<const lds_i32x4 *>(p);
+    }
+    template <int NF>
+    __device__ __forceinline__ static void read_rows(PhFrag<C, NF> &o,
+                                                     uint32_t p0,
+                                                     uint32_t p1) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const i32x4 lo = ld(p0 + f * 2048), hi = ld(p1 + f * 2048);
+            if constexpr (FA::F8) {
+                o.v[f][0] = i32x8{lo[0], lo[1], lo[2], lo[3],
+                                  hi[0], hi[1], hi[2], hi[3]};
+            } else {
+                o.v[f][0] = lo;
+                o.v[f][1] = hi;
+            }
+        }
+    }
+    __device__ __forceinline__ void read(FA &a, FB &b, uint32_t stage) const {
+        read_rows(a, aoff[0] + stage, aoff[1] + stage);
+        if constexpr (MIX) {      // codes, see decode()
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+                b.v[f][0] = ld(boff[0] + stage + f * 1024);
+        } else {
+            read_rows(b, boff[0] + stage, boff[1] + stage);
+        }
+    }
+    __device__ __forceinline__ static void decode(FB &b) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const i32x4 w = b.v[f][0];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const uint2 lo = e4m3x4_to_bf16x4(w[2 * q]);
+                const uint2 hi = e4m3x4_to_bf16x4(w[2 * q + 1]);
+                b.v[f][q] = i32x4{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
+            }
+        }
+    }
+
+    template <class P>
+    __device__ __forceinline__ void run(const P &prov, char *s) {
+        const int G = prov.n_prog(), total = prov.count();
+        int t = program_slot(blockIdx.x, G);
+        if (t >= total) return;
+        init(s);
+        int njob = 0;
+        Acc acc;
+        FA a;
+        FB b;
+        set_job(prov.job(t));
+        tg::issue_scales<C>(j, scale_slot<C>(smem, 0), wave, lane);
+        issue_first();
+        while (true) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) mfma_zero(acc[i >> 2][i & 3]);
+            wait_vmem();      // also the previous sub-tensor's stores
+            slot_end();
+            if (!MIX && j.K % C::EPC != 0) {
+                fill_tail();
+                __syncthreads();
+            }
+            if (wave >> 2) slot_end();        // one slot behind
+#pragma unroll 1
+            for (int q = 0; q < nk; ++q) {
+                // Memory slot.  The stage loaded into was last read by the
+                // group behind in the slot before, which ended after its
+                // data had arrived.
+                read(a, b, (q & 3) * STG);
+                const bool more_k = q + 3 < nk;
+                if (more_k) issue_a(q + 3);
+                // the next tile has landed (B's loads of tile q + 3 come in
+                // the compute slot)
+                const int after = nk - 2 - q;
+                if (__builtin_expect(after >= 2, 1)) wait_vmem_le<LOADS + 2>();
+                else if (after == 1) wait_vmem_le<LOADS>();
+                else wait_vmem();
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if constexpr (MIX) decode(b);
+                slot_end();
+                __builtin_amdgcn_s_setprio(1);
+                if (more_k) issue_b(q + 3);
+                // (decoded fragments are vector-ALU results)
+                if constexpr (MIX) asm volatile("s_nop 1" ::: "memory");
+#pragma unroll
+                for (int h = 0; h < NQ; ++h)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int f = 0; f < 4; ++f)
+                            ph_mfma<C>(a.v[i][h], b.v[f][h], acc[i][f]);
+                __builtin_amdgcn_s_setprio(0);
+                slot_end();
+            }
+            if (!(wave >> 2)) slot_end();     // level again: LDS is free
+            mfma_drain();
+            t += G;
+            const bool more = t < total;
+            const Job done = j;
+            if (more) {
+                set_job(prov.job(t));
+                tg::issue_scales<C>(j, scale_slot<C>(smem, njob + 1), wave,
+                                    lane);
+                issue_first();
+            }
+            if (done.scale_a || done.scale_b)
+                Store::template store<true>(done, acc,
+                                            scale_slot<C>(smem, njob), smem,
+                                            lane, wave);
+            else
+                Store::template store<false>(done, acc, nullptr, smem, lane,
+                                             wave);
+            if (!more) break;
+            ++njob;
+        }
+    }
+};
+
+template <class C>
+__global__ __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_phased128_kernel(
+    GemmArgs g) {
+    extern __shared__ __align__(1024) char smem[];
+    SingleProvider<C> p{g};
+    Phased128<C> k;
+    k.run(p, smem);
+}
+
+template <class C>
+__global__ __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_phased128_grouped_kernel(
+    const GroupProblem *__restrict__ tab, int n, int total, int G) {
+    extern __shared__ __align__(1024) char smem[];
+    GroupProvider<C> p{tab, n, total, G};
+    Phased128<C> k;
+    k.run(p, smem);
+}
+
+template <int DT, bool CBF16>
+VariantEntry entry128() {
+    typedef Cfg<DT, 128, 128, 4, 2, true, CBF16, 128, 4, TG_SCHED_LOCKSTEP> C;
+    VariantEntry e{};
+    e.v.dtype = DT;
+    e.v.bm = C::BM; e.v.bn = C::BN; e.v.bk = C::BK; e.v.stages = C::NS;
+    e.v.sched = TG_SCHED_LOCKSTEP;
+    e.v.wm = C::WM; e.v.wn = C::WN;
+    e.v.b_nk = true; e.v.c_bf16 = CBF16;
+    e.kernel = reinterpret_cast<const void *>(&gemm_phased128_kernel<C>);
+    e.grouped =
+        reinterpret_cast<const void *>(&gemm_phased128_grouped_kernel<C>);
+    e.threads = C::THREADS;
+    e.smem = Phased128<C>::SMEM;
+    return e;
+}
+
+// bf16 by e4m3: one block of 2 x 2 sub-tensors of 64 x 64 per program.
+template <class C>
+struct MixedProvider {
+    const SimpleArgs &g;
+    __device__ int n_prog() const { return g.n_prog; }
+    __device__ int count() const { return g.n_prog; }
+    __device__ Job job(int) const {
+        int bm, bn;
+        simple_block(blockIdx.x, g.n_prog, g.blocks_m, bm, bn);
+        Job j;
+        j.a = static_cast<const char *>(g.a);
+        j.b = static_cast<const char *>(g.b);
+        j.c = g.c;
+        j.scale_a = g.scale_a; j.scale_b = g.scale_b;
+        j.wcount = g.wcount;
+        j.lda = g.lda; j.ldb = g.ldb; j.ldc = g.ldc;
+        j.M = g.M; j.N = g.N; j.K = g.K;
+        j.m0 = bm * 128; j.n0 = bn * 128;
+        j.a_row = j.a + (int64_t)j.m0 * j.lda * 2;
+        j.a_rem = (int64_t)(j.M - j.m0) * j.lda * 2;
+        j.b_row = j.b + (int64_t)j.n0 * j.ldb;
+        j.b_rem = (int64_t)(j.N - j.n0) * j.ldb;
+        return j;
+    }
+};
+
+template <class C>
+__global__ __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_mixed128_kernel(
+    SimpleArgs g) {
+    extern __shared__ __align__(1024) char smem[];
+    MixedProvider<C> p{g};
+    Phased128<C, true> k;
+    k.run(p, smem);
+}
+
+template <bool CBF16>
+hipError_t launch_mixed_out(const SimpleArgs &a, hipStream_t st) {
+    typedef Cfg<TG_BF16, 128, 128, 4, 2, true, CBF16, 128, 4,
+                TG_SCHED_LOCKSTEP> C;
+    constexpr int lds = Phased128<C, true>::SMEM;
+    static const hipError_t ready = hipFuncSetAttribute(
+        reinterpret_cast<const void *>(&gemm_mixed128_kernel<C>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (ready != hipSuccess) return ready;
+    hipLaunchKernelGGL(gemm_mixed128_kernel<C>, dim3((unsigned)a.n_prog),
+                       dim3(C::THREADS), lds, st, a);
+    return hipGetLastError();
 }
 
 template <int DT, bool BNK, bool CBF16>
@@ -767,9 +1169,18 @@ const VariantEntry *phased_entries(int *n) {
         entry<TG_FP8_E4M3, true, false>(), entry<TG_FP8_E4M3, true, true>(),
         entry<TG_BF16, true, false>(TG_SCHED_CROSS_WARM),
         entry<TG_BF16, true, true>(TG_SCHED_CROSS_WARM),
+        entry128<TG_BF16, false>(), entry128<TG_BF16, true>(),
+        entry128<TG_FP8_E4M3, false>(), entry128<TG_FP8_E4M3, true>(),
     };
     *n = (int)(sizeof e / sizeof e[0]);
     return e;
+}
+
+// (checked on the host: blocks of 128 x 128, aligned rows, K of whole chunks
+// of both operands, offsets below 2^31 within a block)
+hipError_t launch_mixed(const SimpleArgs &a, hipStream_t st) {
+    return a.c_bf16 ? launch_mixed_out<true>(a, st)
+                    : launch_mixed_out<false>(a, st);
 }
 
 }  // namespace tg

@@ -1526,7 +1526,8 @@ std::vector<VariantEntry> all_entries() {
         TG_VARIANTS_STG(TG_BF16, 256, 256),
         TG_VARIANTS_BLK(TG_BF16, 256, 256, 2, 2, 64, 4),
         TG_VARIANTS_BLK(TG_BF16, 256, 256, 2, 4, 64, 4),
-        TG_VARIANTS_FOR(TG_BF16, 128, 128, 2, 4, 128, 4),
+        make_entry<Cfg<TG_BF16, 128, 128, 2, 4, false, false, 128, 4>>(),
+        make_entry<Cfg<TG_BF16, 128, 128, 2, 4, false, true, 128, 4>>(),
         TG_VARIANTS_FOR(TG_BF16, 128, 128, 2, 2, 64, 4),
         TG_VARIANTS_FOR(TG_BF16, 128, 128, 2, 2, 128, 2),
         TG_VARIANTS_FOR(TG_BF16, 64, 64, 2, 2, 128, 2),
@@ -1542,7 +1543,6 @@ std::vector<VariantEntry> all_entries() {
         TG_VARIANTS_PP_NK(TG_FP8_E4M3, 256, 256, 64, 4),
         TG_VARIANTS_NK(TG_FP8_E4M3, 256, 256, 2, 4, 64, 4),
         TG_VARIANTS_NK(TG_FP8_E4M3, 128, 128, 2, 2, 128, 2),
-        TG_VARIANTS_NK(TG_FP8_E4M3, 128, 128, 2, 4, 128, 4),
         TG_VARIANTS_NK(TG_FP8_E4M3, 64, 64, 2, 2, 128, 2),
         TG_VARIANTS_NK(TG_FP8_E4M3, 64, 64, 2, 2, 128, 4),
         TG_VARIANTS_NK(TG_FP8_E4M3, 32, 32, 1, 1, 128, 2),

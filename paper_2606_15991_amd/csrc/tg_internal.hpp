@@ -167,6 +167,9 @@ struct SimpleArgs {
     int32_t blocks_m;    // programs per block column
     int32_t n_prog;
 };
+// The same product of bf16 rows with e4m3 weights stored N x K, in programs
+// of 2 x 2 sub-tensors of 64 x 64, on the phased 128 x 128 kernel.
+hipError_t launch_mixed(const SimpleArgs &a, hipStream_t st);
 hipError_t launch_simple(const SimpleArgs &a, hipStream_t st);
 
 // Split of f32 operands into bf16 planes for the BF16xN precisions.

@@ -287,12 +287,17 @@ int64_t tiles_of(int64_t M, int64_t N, int s) {
 //      154; but 2816 x 2560 x 3000 (110) 63 against 59, 2048^3 42 against 27.
 //      Not for outputs of at most 128 rows or columns (64 x 65536 x 512: 19
 //      against 15 with 64);
-//  128: bf16, eight wavefronts and four stages, from eleven in twenty compute
-//      units on: 1536^3 (t(128) = 144) 19.6 us against 22.6 with 64, 512 x
-//      5120 x 5120 (160) 52.6 against 65, but 256 x 8192 x 4096 (128) 42.8
-//      against 39.7; two stages (two programs per compute unit) past one
-//      round: 2304^3 (324) 37.6 against 47 with 256.  e4m3, four wavefronts
-//      and two stages, from three in four on: 1536^3 (144) 12.0 against 11.0;
+//  128: one round in the phased kernel (B stored N x K): bf16 from a quarter
+//      of the compute units on, 1024^2 x 4096 (t(128) = 64) 30.4 us against
+//      32.0 with 64, 256 x 8192 x 4096 (128) 30.5 against 39.4, 512 x 5120 x
+//      5120 (160) 37.6 against 64.8, but 256 x 2560 x 2560 (40) 20.4 both;
+//      e4m3, whose 64 reads half the bytes, from eleven in twenty on: 512 x
+//      5120 x 5120 24.4 against 28.9, 1536^3 (144) 10.2 against 10.7, but
+//      1024 x 1536 x 4096 (96) 20.3 against 18.5.  bf16 K x N (eight
+//      wavefronts in step, four stages) from eleven in twenty: 1536^3 18.7
+//      against 22.4, 256 x 8192 x 4096 41.0 against 38.8.  Past one round
+//      two programs of two stages per compute unit: 2304^3 (324) 37.7
+//      against 39.3 in two rounds of the phased kernel;
 //  64: four stages where all programs are then resident at once (two per
 //      compute unit) and there are at least 36 K tiles: bf16 128 x 5120 x
 //      5120 38 us against 54, 64 x 4096 x 4096 30.8 against 43; but bf16
@@ -310,7 +315,8 @@ int64_t tiles_of(int64_t M, int64_t N, int s) {
 struct DefaultTile {
     int size, stages;
 };
-DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, int cus) {
+DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, bool b_nk,
+                         int cus) {
     if (cus <= 0) cus = 256;
     const auto t = [&](int s) {
         return ((M + s - 1) / s) * ((N + s - 1) / s);
@@ -324,7 +330,7 @@ DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, int cus) {
     if (side > 128 && t(128) > cus && (2 * t(256) >= cus || t(128) > 2 * cus))
         return {256, 0};
     if (side > 64 &&
-        t(128) * 20 >= (int64_t)cus * (dt == TG_BF16 ? 11 : 15))
+        t(128) * 20 >= (int64_t)cus * (dt == TG_BF16 && b_nk ? 5 : 11))
         return {128, t(128) > cus ? 2 : 0};
     const bool deep = t(64) <= 2 * cus && nk >= 36;
     if (deep || t(64) * 4 >= (int64_t)cus * 3) return {64, deep ? 4 : 2};
@@ -407,6 +413,20 @@ void simple_group(Launch &L, const tg_config &cfg, int cus) {
     const int64_t progs = (int64_t)((L.s.tiles_m + 1) / 2) *
                           ((L.s.tiles_n + 1) / 2);
     if (2 * progs >= cus) L.gm = L.gn = 2;
+}
+
+// bf16 rows by e4m3 weights in blocks of 2 x 2 sub-tensors: the phased kernel
+// takes what its 16-byte direct loads can (512 x 5120 x 5120 44 us against
+// 49 through registers).
+bool mixed_ok(const Problem &p, const tg_in *A, const tg_in *B,
+              const tg_out *C, const Launch &L) {
+    const int64_t lim = (int64_t)1 << 31;
+    return p.a_dt == TG_BF16 && p.b_dt == TG_FP8_E4M3 && p.b_nk &&
+           L.gm == 2 && L.gn == 2 && L.cfg.bm == 64 && L.cfg.bn == 64 &&
+           p.K > 0 && p.K % 16 == 0 && aligned16(A->data) &&
+           aligned16(B->data) && (A->rows == 1 || A->ld % 8 == 0) &&
+           (B->rows == 1 || B->ld % 16 == 0) && A->ld * 2 * 256 < lim &&
+           B->ld * 256 < lim && C->ld * 4 * 256 < lim;
 }
 
 // `have`: workspace bytes the caller supplies; the default K split of a
@@ -596,7 +616,7 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
                         "multiple of 16 bytes, e4m3 B stored N x K");
         if (cfg.bm == 0 && cfg.bn == 0) {
             const DefaultTile t =
-                default_tile(L.gemm_dt, p.M, p.N, L.Kc, cus);
+                default_tile(L.gemm_dt, p.M, p.N, L.Kc, p.b_nk, cus);
             cfg.bm = cfg.bn = t.size;
             if (cfg.wm == 0 && cfg.wn == 0 && cfg.bk == 0 &&
                 cfg.stages == 0 && cfg.sched == 0)
@@ -1166,7 +1186,8 @@ tg_status tile_gemm(const tg_in *A, const tg_in *B, tg_out *C,
         a.gm = L.gm; a.gn = L.gn;
         a.blocks_m = simple_blocks_m(L);
         a.n_prog = L.s.n_prog;
-        e = launch_simple(a, hs);
+        e = mixed_ok(p, A, B, C, L) ? launch_mixed(a, hs)
+                                    : launch_simple(a, hs);
         return e == hipSuccess ? TG_OK : hip_fail(e, "simple kernel launch");
     }
 

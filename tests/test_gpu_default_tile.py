@@ -47,10 +47,10 @@ def test_f32_tiles(tile, nk, M, N, K):
     (BF, 2048, 2048, 72, 128, 4),     # t(128) = 256
     (BF, 129, 65536, 72, 256, 2), (BF, 128, 65536, 72, 128, 2),
     (BF, 64, 65536, 72, 64, 2),       # at most 64 rows
-    (BF, 1408, 1664, 72, 128, 4),     # t(128) = 143 >= 140.8
-    (BF, 1408, 1536, 72, 64, 2),      # t(128) = 132, t(64) = 528
-    (F8, 1408, 1664, 144, 64, 2),     # e4m3: 128 from t(128) = 192 on
-    (F8, 1536, 2048, 144, 128, 2),
+    (BF, 1024, 1024, 72, 128, 4),     # t(128) = 64
+    (BF, 1024, 896, 72, 64, 2),       # t(128) = 56, t(64) = 224
+    (F8, 1408, 1664, 144, 128, 4),    # e4m3: t(128) = 143 >= 140.8
+    (F8, 1408, 1536, 144, 64, 2),     # t(128) = 132, t(64) = 528
     (BF, 130, 300, 2304, 64, 4), (BF, 130, 300, 2296, 32, 2),
     (F8, 130, 300, 4608, 64, 4), (F8, 130, 300, 4592, 32, 2),
     (F32, 32, 20000, 36, 32, 2), (F32, 33, 20000, 36, 64, 2),
