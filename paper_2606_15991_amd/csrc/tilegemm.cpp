@@ -288,9 +288,9 @@ int64_t tiles_of(int64_t M, int64_t N, int s) {
 //      Not for outputs of at most 128 rows or columns (64 x 65536 x 512: 19
 //      against 15 with 64);
 //  128: one round in the phased kernel (B stored N x K): bf16 from a quarter
-//      of the compute units on, 1024^2 x 4096 (t(128) = 64) 30.4 us against
-//      32.0 with 64, 256 x 8192 x 4096 (128) 30.5 against 39.4, 512 x 5120 x
-//      5120 (160) 37.6 against 64.8, but 256 x 2560 x 2560 (40) 20.4 both;
+//      of the compute units on, 256 x 8192 x 4096 (t(128) = 128) 30.5 us
+//      against 39.4 with 64, 512 x 5120 x 5120 (160) 37.6 against 64.8, 1280^3
+//      (100) 13.2 against 15.0;
 //      e4m3, whose 64 reads half the bytes, from eleven in twenty on: 512 x
 //      5120 x 5120 24.4 against 28.9, 1536^3 (144) 10.2 against 10.7, but
 //      1024 x 1536 x 4096 (96) 20.3 against 18.5.  bf16 K x N (eight
@@ -299,11 +299,10 @@ int64_t tiles_of(int64_t M, int64_t N, int s) {
 //      two programs of two stages per compute unit: 2304^3 (324) 37.7
 //      against 39.3 in two rounds of the phased kernel;
 //  64: four stages where all programs are then resident at once (two per
-//      compute unit) and there are at least 36 K tiles: bf16 128 x 5120 x
-//      5120 38 us against 54, 64 x 4096 x 4096 30.8 against 43; but bf16
-//      1536^3 (t(64) = 576) 31.5 against 22.6 and e4m3 200 x 300 x 4000 (31
-//      K tiles) 15.8 against 14.8;
-//  32 where 64 leaves a quarter of the compute units idle and K is shorter.
+//      compute unit) and there are at least 36 K tiles: bf16 K x N 256 x 8192
+//      x 4096 38.8 us against 44.6; but 1536^3 (t(64) = 576) 31.5 against
+//      22.6 and e4m3 1280^3 (10 K tiles) 8.6 against 8.2;
+//  32 where 64 leaves a quarter of the compute units idle.
 // f32 is bound by the matrix instructions alone, so the busiest compute unit
 // decides: ceil(t / cus) rounds at 36 us (64) and 128 us (128) for K = 2048:
 //  128 where two of its rounds take no longer than seven of 64: 2048^3 (1 and
@@ -312,8 +311,19 @@ int64_t tiles_of(int64_t M, int64_t N, int s) {
 //      (3, 1) 275 against 342, 1000 x 3000 x 2000 (3, 1) 112 against 138;
 //  32 is never ahead (512^3 16.5 us against 15.6, 130 x 3000 x 256 10.0
 //      against 9.7) and is left to outputs of at most 32 rows or columns.
+// First of all, outputs of at most one sub-tensor per compute unit take the
+// programs whose wavefronts share K (wm = 8 of 32 x 32, 4 of 64 x 64), from
+// four and eight K tiles on:
+//  32  t(32) <= cus: bf16 300 x 300 x 8192 14.4 us against 57 (64, four
+//      stages), 64 x 4096 x 4096 9.4 against 30; e4m3 512^3 (four K tiles)
+//      3.6 against 4.1, but 128^3 (one) 3.2 against 2.9; f32 up to three
+//      rounds: 512^3 5.7 against 14.7, 800^2 x 2048 (t(32) = 625) 37 against
+//      50, but 1024^3 (1024) 28.8 against 26.9;
+//  64  t(64) <= cus: bf16 1024^3 7.3 us against 10.4, 1024^2 x 4096 15.8
+//      against 30.6 (128), 256 x 2560 x 2560 10.7 against 20.4; e4m3 1024^3
+//      (eight) 5.8 against 6.1, 768^3 (six) 5.2 against 5.1.
 struct DefaultTile {
-    int size, stages;
+    int size, stages, wm = 0;
 };
 DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, bool b_nk,
                          int cus) {
@@ -323,10 +333,13 @@ DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, bool b_nk,
     };
     if (dt == TG_F32) {
         const auto rounds = [&](int s) { return (t(s) + cus - 1) / cus; };
+        if (t(32) <= 3 * (int64_t)cus && K * 4 >= 4 * 128) return {32, 16, 8};
         if (std::min(M, N) <= 32) return {32, 0};
         return {2 * rounds(64) >= 7 * rounds(128) ? 128 : 64, 0};
     }
     const int64_t nk = K * esize(dt) / 128, side = std::min(M, N);
+    if (t(32) <= cus && nk >= 4) return {32, 16, 8};
+    if (t(64) <= cus && nk >= 8) return {64, 8, 4};
     if (side > 128 && t(128) > cus && (2 * t(256) >= cus || t(128) > 2 * cus))
         return {256, 0};
     if (side > 64 &&
@@ -619,8 +632,10 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
                 default_tile(L.gemm_dt, p.M, p.N, L.Kc, p.b_nk, cus);
             cfg.bm = cfg.bn = t.size;
             if (cfg.wm == 0 && cfg.wn == 0 && cfg.bk == 0 &&
-                cfg.stages == 0 && cfg.sched == 0)
+                cfg.stages == 0 && cfg.sched == 0) {
                 cfg.stages = t.stages;
+                cfg.wm = t.wm;
+            }
         } else if (cfg.bm == 0 || cfg.bn == 0) {
             return fail(TG_E_ARG, "config bm/bn: set both or neither");
         }
