@@ -307,14 +307,9 @@ __global__ __launch_bounds__(128 * waves_n(BM)) void gemm_simple_kernel(SimpleAr
                 }
         }
     };
-    // Tiles 0 .. nf - 1 load without checks: they lie inside K and, where
-    // this block's columns of a k-major B end with a partial chunk, in front
-    // of the operand's last row (the partial chunks then run on into the
-    // next row, at most EPC - 1 <= ld elements).
-    constexpr int EPCB = Src<BDT>::EPC;
-    int nf = g.K / BK;
-    if (!BNK && n0 + BN > g.N && g.N % EPCB)
-        nf = g.N >= EPCB && g.K > 0 ? (g.K - 1) / BK : 0;
+    // tiles 0 .. nf - 1 load without checks
+    const int nf = simple_whole_tiles(g.K, BK, BNK, g.N, n0, BN,
+                                      Src<BDT>::EPC);
     auto load = [&](int s, int kt) {
         const int k0 = min(kt, nf - 1) * BK;   // past the last: unused
         la.load(s, k0, g.lda);

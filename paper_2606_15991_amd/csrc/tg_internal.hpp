@@ -64,6 +64,20 @@ __host__ __device__ inline void simple_block(int32_t p, int32_t n_prog,
     bn = t / blocks_m;
 }
 
+// Simple kernel: leading K tiles of bk that a program loads without checks.
+// All whole ones, except where a chunk of epc elements straddles column N of
+// a B stored K x N (the program's columns start at n0, any multiple of the
+// caller's partition, and it loads bn of them): such a chunk runs on into the
+// next row, at most epc - 1 elements, so the tile with the last row, and
+// rows shorter than a chunk, are left to the checked loads.
+__host__ __device__ inline int32_t simple_whole_tiles(int32_t K, int32_t bk,
+                                                      bool b_nk, int32_t N,
+                                                      int32_t n0, int32_t bn,
+                                                      int32_t epc) {
+    if (b_nk || N - n0 >= bn || (N - n0) % epc == 0) return K / bk;
+    return N >= epc && K > 0 ? (K - 1) / bk : 0;
+}
+
 // Kernel arguments of one tiled product.
 struct GemmArgs {
     const void *a;
