@@ -14,11 +14,12 @@
 // registers while one is contracted (one program of four wavefronts per
 // SIMD group hides little latency by itself), then converted and stored to
 // the other LDS buffer, one barrier per tile.  Global reads are 16 bytes per
-// lane (8 of e4m3) from the dword below the chunk; where a row may start
-// inside a dword (SHIFT) one more dword is read and the chunk shifted into
-// place, since the unaligned access mode's own handling of such addresses
-// takes about a cycle per lane (37.1 us with it, 21.7 with the shift at
-// bf16 1111 x 1531 x 1003, B stored K x N).  No dword without a byte of the operand is touched.
+// lane (8 of e4m3) from the dword below the chunk; where a chunk may start
+// inside a dword (SHIFT: its row does, or for B stored K x N the partition's
+// columns do) one more dword is read and the chunk shifted into place, since
+// the unaligned access mode's own handling of such addresses takes about a
+// cycle per lane (37.1 us with it, 21.7 with the shift at bf16 1111 x 1531 x
+// 1003, B stored K x N).  No dword without a byte of the operand is touched.
 // Direct-to-LDS loads need aligned rows and no conversion, so they stay with
 // the tiled kernel.  The K tile with chunks that straddle the end of K (or,
 // for B stored K x N, the operand's last row where chunks straddle N) is
@@ -398,15 +399,13 @@ hipError_t launch_blocks(const SimpleArgs &a, hipStream_t st) {
                : launch_block<ADT, BDT, BNK, 64, 64, SHIFT>(a, st);
 }
 
-// Does any row of the operand start inside a dword?
-bool row_shift(const void *p, int64_t ld, int dt) {
-    const int64_t es = dt == TG_F32 ? 4 : dt == TG_BF16 ? 2 : 1;
-    return (reinterpret_cast<uintptr_t>(p) | (uintptr_t)(ld * es)) & 3;
-}
-
 template <int ADT, int BDT>
 hipError_t launch_layout(const SimpleArgs &a, hipStream_t st) {
-    const bool sh = row_shift(a.a, a.lda, ADT) || row_shift(a.b, a.ldb, BDT);
+    const bool sh =
+        simple_shift(reinterpret_cast<uintptr_t>(a.a), a.lda, Src<ADT>::ES,
+                     0) ||
+        simple_shift(reinterpret_cast<uintptr_t>(a.b), a.ldb, Src<BDT>::ES,
+                     a.b_nk ? 0 : a.gn * a.bn);
     if (a.b_nk)
         return sh ? launch_blocks<ADT, BDT, true, true>(a, st)
                   : launch_blocks<ADT, BDT, true, false>(a, st);

@@ -78,6 +78,14 @@ __host__ __device__ inline int32_t simple_whole_tiles(int32_t K, int32_t bk,
     return N >= epc && K > 0 ? (K - 1) / bk : 0;
 }
 
+// Simple kernel: does any chunk of an operand start inside a dword?  Rows are
+// ld elements of es bytes apart; programs start at multiples of `step`
+// elements of a row (0: all at its first, chunks along it are whole dwords).
+inline bool simple_shift(uintptr_t base, int64_t ld, int64_t es,
+                         int64_t step) {
+    return ((base | (uint64_t)(ld * es) | (uint64_t)(step * es)) & 3) != 0;
+}
+
 // Kernel arguments of one tiled product.
 struct GemmArgs {
     const void *a;

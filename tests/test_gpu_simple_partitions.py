@@ -41,3 +41,20 @@ def test_straddling_blocks(bm, bn, adt, bdt):
     torch.cuda.synchronize()
     assert torch.all(wc == 1)
     assert np.array_equal(exact64(C.cpu()), reference(A, B))
+
+
+# operands of whole dwords (no shifting of chunks), default partition: one
+# 64 x 64 block a program, and 2 x 2 of them (more than 128 programs of those)
+@pytest.mark.parametrize("M,N,K", [(33, 136, 132), (1400, 1500, 132)])
+@pytest.mark.parametrize("adt,bdt", [(BF, BF), (BF, F8), (F8, F8),
+                                     (F32, F32)])
+@pytest.mark.parametrize("b_trans", [True, False])
+def test_whole_dwords(M, N, K, adt, bdt, b_trans):
+    note("simple whole dwords", M, N, K, adt, bdt, b_trans)
+    A = synth.small_int((M, K), 93).to(adt)
+    B = synth.small_int((N, K) if b_trans else (K, N), 94).to(bdt)
+    C = torch.full((M, N), float("nan"), device=DEV)
+    tg.tile_gemm(fenced(A), fenced(B), C, b_trans=b_trans,
+                 config={"kind": "simple"})
+    torch.cuda.synchronize()
+    assert np.array_equal(exact64(C.cpu()), reference(A, B, b_trans))

@@ -19,6 +19,9 @@ extern "C" int whole_tiles(int K, int bk, int b_nk, int N, int n0, int bn,
                            int epc) {
     return tg::simple_whole_tiles(K, bk, b_nk, N, n0, bn, epc);
 }
+extern "C" int shift(uintptr_t base, int64_t ld, int64_t es, int64_t step) {
+    return tg::simple_shift(base, ld, es, step);
+}
 """
 
 
@@ -59,3 +62,18 @@ def test_unchecked_loads_stay_inside(rules, es, epc, bk, N):
                 if N - n0 >= BN or (N - n0) % epc == 0:
                     assert t == K // bk
                 assert rules.whole_tiles(K, bk, 1, N, n0, BN, epc) == K // bk
+
+
+@pytest.mark.parametrize("es,epc", [(4, 4), (2, 8), (1, 8)])
+def test_unshifted_chunks_are_whole_dwords(rules, es, epc):
+    i64 = ctypes.c_int64
+    rules.shift.argtypes = [ctypes.c_size_t, i64, i64, i64]
+    for base in range(0, 8, es):
+        for ld in range(128, 136):
+            for step in range(0, 65):
+                n0 = step * np.arange(4)
+                k = np.arange(8)
+                at = base + (k[:, None, None] * ld + n0[:, None] +
+                             np.arange(0, 64, epc)) * es
+                assert bool(rules.shift(base, ld, es, step)) == \
+                    bool((at % 4).any()), (base, ld, step)
