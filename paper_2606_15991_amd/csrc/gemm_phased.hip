@@ -92,6 +92,15 @@ __device__ __forceinline__ void mfma_drain() {
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 }
 
+// At most N LDS accesses of this wavefront in flight (vmcnt and expcnt at
+// their no-wait maxima).
+template <int N>
+__device__ __forceinline__ void wait_lds_le() {
+    static_assert(N >= 0 && N < 16, "lgkmcnt range");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (N << 8));
+}
+
 __device__ __forceinline__ void slot_end() {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
@@ -642,12 +651,16 @@ struct Phased {
     // so_b: offsets along K of A's next tile and of both operands' tile two
     // further on.
     //
-    // Reuse: a half read in memory slot i by the first group is read in the
-    // next slot by the second, whose data have arrived by the end of its
-    // compute slot, i.e. before the first group's memory slot i + 2.  So a
-    // half may be loaded over from memory slot i + 2: B half 0 (read in the
-    // last phase of the tile before) in phase 2, A half 0 in phase 3, B half
-    // 1 in phase 4, A half 1 in phase 1 of the next tile.
+    // Reuse, counted in slots: A half 0, B half 1 and A half 1 are read in the
+    // memory slots of phases 1, 2 and 3 and contracted in the slot after, so
+    // the second group, one slot behind, has their data two slots after the
+    // first group read them; they are loaded over in the first group's
+    // memory slots of phases 3, 4 and 1 of the next tile, four slots after.
+    // B half 0 is read in phase 4 but contracted only in phase 1 of the next
+    // tile, four slots on for the second group, which would be the very slot
+    // in which the first group loads over it (phase 2): hence the wait for
+    // it at the end of phase 1's memory slot, with phase 1's own eight reads
+    // still in flight (a wavefront's LDS reads return in order).
     template <int S>
     __device__ __forceinline__ void tile(FA &a, FB &x, FB &y, Acc &acc,
                                          int left, int so_a1, int so_a,
@@ -655,6 +668,7 @@ struct Phased {
         read_a<S>(a, 0);
         if (__builtin_expect(left > 1, 1)) issue_a<1 - S, 1>(so_a1);
         wait_loads<10, 2>(left);
+        wait_lds_le<8>();
         slots<0, 0>(a, x, acc);
         read_b<S>(y, 1);
         if (__builtin_expect(left > 2, 1)) {
