@@ -1094,8 +1094,9 @@ VariantEntry entry128() {
     e.v.wm = C::WM; e.v.wn = C::WN;
     e.v.b_nk = true; e.v.c_bf16 = CBF16;
     e.kernel = reinterpret_cast<const void *>(&gemm_phased128_kernel<C>);
-    e.grouped =
-        reinterpret_cast<const void *>(&gemm_phased128_grouped_kernel<C>);
+    if constexpr (DT == TG_BF16)
+        e.grouped =
+            reinterpret_cast<const void *>(&gemm_phased128_grouped_kernel<C>);
     e.threads = C::THREADS;
     e.smem = Phased128<C>::SMEM;
     return e;
@@ -1161,10 +1162,12 @@ VariantEntry entry(int sched = TG_SCHED_CROSS) {
     e.v.wm = C::WM; e.v.wn = C::WN;
     e.v.b_nk = BNK; e.v.c_bf16 = CBF16;
     e.kernel = reinterpret_cast<const void *>(&gemm_phased_kernel<C, false>);
-    if constexpr (DT == TG_BF16)
+    if constexpr (DT == TG_BF16) {
         e.planes =
             reinterpret_cast<const void *>(&gemm_phased_kernel<C, true>);
-    e.grouped = reinterpret_cast<const void *>(&gemm_phased_grouped_kernel<C>);
+        e.grouped =
+            reinterpret_cast<const void *>(&gemm_phased_grouped_kernel<C>);
+    }
     e.threads = C::THREADS;
     e.smem = Phased<C>::SMEM;
     return e;

@@ -1579,8 +1579,9 @@ VariantEntry entry_ksplit() {
     e.v.wm = W; e.v.wn = 1;
     e.v.b_nk = BNK; e.v.c_bf16 = CBF16;
     e.kernel = reinterpret_cast<const void *>(&gemm_ksplit_kernel<C, W>);
-    e.grouped =
-        reinterpret_cast<const void *>(&gemm_ksplit_grouped_kernel<C, W>);
+    if constexpr (DT == TG_BF16)
+        e.grouped =
+            reinterpret_cast<const void *>(&gemm_ksplit_grouped_kernel<C, W>);
     e.threads = W * 64;
     e.smem = W * C::NS * C::STAGE;
     return e;
@@ -1598,7 +1599,8 @@ VariantEntry make_entry() {
     e.v.wm = C::WM; e.v.wn = C::WN;
     e.v.b_nk = C::BNK; e.v.c_bf16 = C::CBF16;
     e.kernel = reinterpret_cast<const void *>(&gemm_tiled_kernel<C>);
-    e.grouped = reinterpret_cast<const void *>(&gemm_grouped_kernel<C>);
+    if constexpr (C::DTYPE == TG_BF16)
+        e.grouped = reinterpret_cast<const void *>(&gemm_grouped_kernel<C>);
     e.threads = C::THREADS;
     e.smem = C::SMEM;
     return e;
@@ -1717,7 +1719,7 @@ static hipError_t prepare_smem(const VariantEntry &e) {
         return hipSuccess;
     hipError_t err = hipFuncSetAttribute(
         e.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, e.smem);
-    if (err == hipSuccess)
+    if (err == hipSuccess && e.grouped)
         err = hipFuncSetAttribute(
             e.grouped, hipFuncAttributeMaxDynamicSharedMemorySize, e.smem);
     if (err == hipSuccess && e.planes)
@@ -1748,6 +1750,7 @@ hipError_t launch_grouped(int variant, int n_problems, int total_tiles,
                           int n_prog, const void *table_dev, hipStream_t st) {
     int n;
     const VariantEntry &e = table(&n)[variant];
+    if (!e.grouped) return hipErrorInvalidValue;
     hipError_t err = prepare_smem(e);
     if (err != hipSuccess) return err;
     const GroupProblem *tab = static_cast<const GroupProblem *>(table_dev);

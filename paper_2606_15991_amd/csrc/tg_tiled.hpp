@@ -11,7 +11,7 @@ namespace tg {
 struct VariantEntry {
     TiledVariant v;
     const void *kernel;
-    const void *grouped;
+    const void *grouped = nullptr;  // bf16 only (grouped launches take no other)
     int threads;
     int smem;
     const void *planes = nullptr;   // products of planes (GemmArgs::kp)
