@@ -97,3 +97,18 @@ def test_accumulators_stay_in_their_registers(assembly):
                            for l in acc), name
         first = next(i for i, l in enumerate(body) if "accvgpr" in l)
         assert "s_nop 15" in body[:first], name
+
+
+REMARKS = """x.hip:9:1: remark: Function Name: _Z1av [-Rpass-analysis]
+x.hip:9:1: remark:     ScratchSize [bytes/lane]: %d [-Rpass-analysis]
+x.hip:9:1: remark:     SGPRs Spill: 3 [-Rpass-analysis]
+x.hip:9:1: remark:     VGPRs Spill: %d [-Rpass-analysis]
+"""
+
+
+def test_the_build_refuses_spills():
+    assert "gemm_phased.hip" in lib_build.NO_SPILL
+    lib_build.check_no_spill("x.hip", REMARKS % (0, 0) + REMARKS % (0, 0))
+    for bad in (REMARKS % (0, 0) + REMARKS % (8, 0), REMARKS % (0, 1), ""):
+        with pytest.raises(RuntimeError):
+            lib_build.check_no_spill("x.hip", bad)
