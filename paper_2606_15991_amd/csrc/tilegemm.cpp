@@ -211,6 +211,14 @@ tg_status describe(const tg_in *A, const tg_in *B, const tg_out *C,
     return TG_OK;
 }
 
+// A single row has no stride, and check_in takes any for it; the kernels size
+// their buffers by it.
+tg_in row_stride(const tg_in &d) {
+    tg_in r = d;
+    if (r.rows <= 1 && r.ld < r.cols) r.ld = r.cols;
+    return r;
+}
+
 bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Can the tiled kernel take this operand layout?
@@ -231,7 +239,9 @@ bool tiled_ok(const Problem &p, const tg_in *A, const tg_in *B,
     // the kernels address a sub-tensor with 32-bit byte offsets: 256 rows of
     // any operand (and of C in binary32) must span less than 2^31 bytes
     const int64_t lim = (int64_t)1 << 31;
-    if (A->ld * es * 256 >= lim || B->ld * es * 256 >= lim) return false;
+    if (row_stride(*A).ld * es * 256 >= lim ||
+        row_stride(*B).ld * es * 256 >= lim)
+        return false;
     if (C->ld * 4 * 256 >= lim) return false;
     return true;
 }
@@ -1137,6 +1147,9 @@ tg_status tile_gemm(const tg_in *A, const tg_in *B, tg_out *C,
     Problem p;
     tg_status st = describe(A, B, C, o, p);
     if (st != TG_OK) return st;
+    const tg_in a_row = row_stride(*A), b_row = row_stride(*B);
+    A = &a_row;
+    B = &b_row;
     Launch L;
     const size_t have = o && o->workspace ? o->workspace_bytes : 0;
     if ((st = choose(p, A, B, C, o, L, have)) != TG_OK) return st;
@@ -1437,7 +1450,8 @@ tg_status tile_gemm_grouped_prepare(int32_t n, const tg_in *A,
         int32_t i = order[r];
         GroupProblem &g = tab[r];
         g.a = A[i].data; g.b = B[i].data; g.c = C[i].data;
-        g.lda = A[i].ld; g.ldb = B[i].ld; g.ldc = C[i].ld;
+        g.lda = row_stride(A[i]).ld; g.ldb = row_stride(B[i]).ld;
+        g.ldc = C[i].ld;
         g.M = (int32_t)ps[i].M; g.N = (int32_t)ps[i].N; g.K = (int32_t)ps[i].K;
         g.tiles_m = (int32_t)((ps[i].M + cfg.bm - 1) / cfg.bm);
         g.tiles_n = (int32_t)((ps[i].N + cfg.bn - 1) / cfg.bn);
