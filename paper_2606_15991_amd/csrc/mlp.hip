@@ -197,6 +197,7 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_fused(MlpArgs g) {
     const int kc0 = (g.n_in + 15) >> 4, kch = (H + 15) >> 4;
     // fixed roles: forward / input gradients, one 16 x 16 tile per wavefront
     const int mt = (wave >> 2) * 16, nt = (wave & 3) * 16;
+    const bool pad = nt + lr >= H;
     // weight gradients, two 16 x 16 tiles per wavefront and layer
     const int ot = (wave >> 1) * 16, it = (wave & 1) * 32;
     // column sums: column tid % 64 over the four rows of part tid / 64
@@ -236,8 +237,9 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_fused(MlpArgs g) {
             for (int v = 0; v < 4; ++v) {
                 const int r = mt + 4 * q4 + v;
                 const float s = acc[v];
-                // rows past the batch stay zero in every layer
-                Y[r * kMlpLd] = r >= valid || s < 0.f ? 0.f : s;
+                // rows past the batch and columns past the layer stay zero
+                // (zero weights alone would make them NaN behind an infinity)
+                Y[r * kMlpLd] = r >= valid || pad || s < 0.f ? 0.f : s;
             }
             __syncthreads();
         }
