@@ -333,6 +333,17 @@ assert _pack.size == ctypes.sizeof(_Frame)
 _NO_IN = (0, 0, 0, 0, 0, 0)
 
 
+def _fill(frame, fields):
+    """Pack the fields of one call; integers wrap as they do in ctypes."""
+    try:
+        _pack.pack_into(frame, 0, *fields)
+    except struct.error:
+        wrap = {"i": ctypes.c_int32, "q": ctypes.c_int64,
+                "P": ctypes.c_size_t, "N": ctypes.c_size_t}
+        _pack.pack_into(frame, 0, *(
+            wrap[f](v).value for f, v in zip(3 * _IN + _OUT + _OPTS, fields)))
+
+
 def _in(t, trans=0):
     """make_in's fields as a tuple."""
     try:
@@ -377,7 +388,7 @@ def _gemm(entry, A, B, C, bm, bn, b_trans, precision, scale_a, scale_b,
     k = _call
     prec = _precision(precision)
     cfg = None if config is None else make_config(config)   # (kept alive)
-    a, b, c = _in(A), _in(B, 1 if b_trans else 0), _in(C)
+    a, b, c = _in(A), _in(B, int(b_trans)), _in(C)
     x, xa = _NO_IN, 0
     if residual is not None:
         x, xa = _in(residual), k.x_addr
@@ -385,7 +396,7 @@ def _gemm(entry, A, B, C, bm, bn, b_trans, precision, scale_a, scale_b,
     out = c + (int(bm), int(bn))
     o = _opts(prec, checked, scale_a, scale_b, cfg, workspace, write_count,
               xa)
-    _pack.pack_into(k.f, 0, *a, *b, *x, *out, *o)
+    _fill(k.f, a + b + x + out + o)
     # only split precisions and decode products (at most 16 rows) take one
     if alloc and workspace is None and (prec or a[3] <= 16):
         need = lib.tile_gemm_workspace_size(k.a, k.b, k.c, k.o)
@@ -394,7 +405,7 @@ def _gemm(entry, A, B, C, bm, bn, b_trans, precision, scale_a, scale_b,
             # (packed again: an allocation may run other code of this thread)
             o = _opts(prec, checked, scale_a, scale_b, cfg, workspace,
                       write_count, xa)
-            _pack.pack_into(k.f, 0, *a, *b, *x, *out, *o)
+            _fill(k.f, a + b + x + out + o)
     st = entry(k.a, k.b, k.c, k.o, h)
     if st:
         _raise(st)
@@ -435,9 +446,9 @@ def tile_gemm_noalloc(A, B, C, bm=0, bn=0, *, b_trans=False,
 
 def _elementwise(entry, x, y, z, bm, bn, checked, write_count, stream):
     k, h = _call, _stream(stream)
-    _pack.pack_into(k.f, 0, *_in(x), *_in(y), *_NO_IN, *_in(z), int(bm),
-                    int(bn), *_opts(TG_PREC_NATIVE, checked, None, None,
-                                    None, None, write_count, 0))
+    _fill(k.f, _in(x) + _in(y) + _NO_IN + _in(z) + (int(bm), int(bn)) +
+          _opts(TG_PREC_NATIVE, checked, None, None, None, None, write_count,
+                0))
     st = entry(k.a, k.b, k.c, k.o, h)
     if st:
         _raise(st)
@@ -469,10 +480,10 @@ def tile_rms_norm(x, w, y, eps=1e-6, bm=0, *, checked=True,
     if w.dim() == 1:
         w = w.view(1, -1)
     k, h = _call, _stream(stream)
-    _pack.pack_into(k.f, 0, *_in(x), *_in(w), *_NO_IN, *_in(y), int(bm),
-                    int(y.shape[1]) if bm else 0,
-                    *_opts(TG_PREC_NATIVE, checked, None, None, None, None,
-                           write_count, 0))
+    _fill(k.f, _in(x) + _in(w) + _NO_IN + _in(y) +
+          (int(bm), int(y.shape[1]) if bm else 0) +
+          _opts(TG_PREC_NATIVE, checked, None, None, None, None, write_count,
+                0))
     st = lib.tile_rms_norm(k.a, k.b, float(eps), k.c, k.o, h)
     if st:
         _raise(st)
@@ -504,10 +515,9 @@ def tile_rms_norm_matvec(x, nw, W, y, eps=1e-6, *, scale_w=None,
     h = _stream(stream)
 
     def fill():
-        _pack.pack_into(k.f, 0, *a, *w, *n, *out, 0, 0,
-                        *_opts(TG_PREC_NATIVE, checked, None, scale_w, None,
-                               given, write_count,
-                               0 if res is None else ctypes.addressof(res)))
+        _fill(k.f, a + w + n + out + (0, 0) +
+              _opts(TG_PREC_NATIVE, checked, None, scale_w, None, given,
+                    write_count, 0 if res is None else ctypes.addressof(res)))
     fill()
     if workspace is None:
         need = lib.tile_rms_norm_matvec_workspace_size(k.a, k.b, k.c)
