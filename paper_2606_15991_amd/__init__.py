@@ -313,9 +313,8 @@ class _Frame(ctypes.Structure):
                 ("o", tg_opts)]
 
 
-class _Call(threading.local):
-    """One frame per thread: the library reads it during the call and keeps
-    nothing of it."""
+class _Held:
+    """A frame, references to its parts, and whether a call is using it."""
 
     def __init__(self):
         f = self.f = _Frame()
@@ -324,9 +323,31 @@ class _Call(threading.local):
         self.c, self.o = ctypes.byref(f.c), ctypes.byref(f.o)
         self.out = f.c
         self.x_addr = ctypes.addressof(f.x)
+        self.busy = False
+
+
+class _Call(threading.local):
+    """One frame per thread: the library reads it during the call and keeps
+    nothing of it."""
+
+    def __init__(self):
+        self.held = _Held()
+        self.f = self.held.f
 
 
 _call = _Call()
+
+
+def _take():
+    """The thread's frame, marked busy until the caller clears the mark; a
+    new one for a call inside another (a signal handler, a finalizer)."""
+    k = _call.held
+    if k.busy:
+        k = _Held()
+    k.busy = True
+    return k
+
+
 _IN, _OUT, _OPTS = "Piiqqq", "Piiqqqii", "iiPPPPNPP"
 _pack = struct.Struct("@" + 3 * _IN + _OUT + _OPTS)
 assert _pack.size == ctypes.sizeof(_Frame)
@@ -385,31 +406,34 @@ def _precision(precision):
 def _gemm(entry, A, B, C, bm, bn, b_trans, precision, scale_a, scale_b,
           config, workspace, alloc, write_count, checked, residual, stream):
     """Fill the frame and call entry; returns the partition."""
-    k = _call
-    prec = _precision(precision)
-    cfg = None if config is None else make_config(config)   # (kept alive)
-    a, b, c = _in(A), _in(B, int(b_trans)), _in(C)
-    x, xa = _NO_IN, 0
-    if residual is not None:
-        x, xa = _in(residual), k.x_addr
-    h = _stream(stream)
-    out = c + (int(bm), int(bn))
-    o = _opts(prec, checked, scale_a, scale_b, cfg, workspace, write_count,
-              xa)
-    _fill(k.f, a + b + x + out + o)
-    # only split precisions and decode products (at most 16 rows) take one
-    if alloc and workspace is None and (prec or a[3] <= 16):
-        need = lib.tile_gemm_workspace_size(k.a, k.b, k.c, k.o)
-        if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=C.device)
-            # (packed again: an allocation may run other code of this thread)
-            o = _opts(prec, checked, scale_a, scale_b, cfg, workspace,
-                      write_count, xa)
-            _fill(k.f, a + b + x + out + o)
-    st = entry(k.a, k.b, k.c, k.o, h)
-    if st:
-        _raise(st)
-    return k.out.bm, k.out.bn
+    k = _take()
+    try:
+        prec = _precision(precision)
+        cfg = None if config is None else make_config(config)  # (kept alive)
+        a, b, c = _in(A), _in(B, int(b_trans)), _in(C)
+        x, xa = _NO_IN, 0
+        if residual is not None:
+            x, xa = _in(residual), k.x_addr
+        h = _stream(stream)
+        out = c + (int(bm), int(bn))
+        o = _opts(prec, checked, scale_a, scale_b, cfg, workspace,
+                  write_count, xa)
+        _fill(k.f, a + b + x + out + o)
+        # only split precisions and decode products (at most 16 rows) take one
+        if alloc and workspace is None and (prec or a[3] <= 16):
+            need = lib.tile_gemm_workspace_size(k.a, k.b, k.c, k.o)
+            if need:
+                workspace = torch.empty(need, dtype=torch.uint8,
+                                        device=C.device)
+                o = _opts(prec, checked, scale_a, scale_b, cfg, workspace,
+                          write_count, xa)
+                _fill(k.f, a + b + x + out + o)
+        st = entry(k.a, k.b, k.c, k.o, h)
+        if st:
+            _raise(st)
+        return k.out.bm, k.out.bn
+    finally:
+        k.busy = False
 
 
 def tile_gemm(A, B, C, bm=0, bn=0, *, b_trans=False, precision="native",
@@ -445,14 +469,18 @@ def tile_gemm_noalloc(A, B, C, bm=0, bn=0, *, b_trans=False,
 
 
 def _elementwise(entry, x, y, z, bm, bn, checked, write_count, stream):
-    k, h = _call, _stream(stream)
-    _fill(k.f, _in(x) + _in(y) + _NO_IN + _in(z) + (int(bm), int(bn)) +
-          _opts(TG_PREC_NATIVE, checked, None, None, None, None, write_count,
-                0))
-    st = entry(k.a, k.b, k.c, k.o, h)
-    if st:
-        _raise(st)
-    return k.out.bm, k.out.bn
+    k = _take()
+    try:
+        h = _stream(stream)
+        _fill(k.f, _in(x) + _in(y) + _NO_IN + _in(z) + (int(bm), int(bn)) +
+              _opts(TG_PREC_NATIVE, checked, None, None, None, None,
+                    write_count, 0))
+        st = entry(k.a, k.b, k.c, k.o, h)
+        if st:
+            _raise(st)
+        return k.out.bm, k.out.bn
+    finally:
+        k.busy = False
 
 
 def tile_add(x, y, z, bm=0, bn=0, *, checked=True, write_count=None,
@@ -479,15 +507,20 @@ def tile_rms_norm(x, w, y, eps=1e-6, bm=0, *, checked=True,
     elements, 1-D or 1 x d), into y's bm x d partition.  Returns y."""
     if w.dim() == 1:
         w = w.view(1, -1)
-    k, h = _call, _stream(stream)
-    _fill(k.f, _in(x) + _in(w) + _NO_IN + _in(y) +
-          (int(bm), int(y.shape[1]) if bm else 0) +
-          _opts(TG_PREC_NATIVE, checked, None, None, None, None, write_count,
-                0))
-    st = lib.tile_rms_norm(k.a, k.b, float(eps), k.c, k.o, h)
-    if st:
-        _raise(st)
-    tile_rms_norm.last_partition = (k.out.bm, k.out.bn)
+    k = _take()
+    try:
+        h = _stream(stream)
+        _fill(k.f, _in(x) + _in(w) + _NO_IN + _in(y) +
+              (int(bm), int(y.shape[1]) if bm else 0) +
+              _opts(TG_PREC_NATIVE, checked, None, None, None, None,
+                    write_count, 0))
+        st = lib.tile_rms_norm(k.a, k.b, float(eps), k.c, k.o, h)
+        if st:
+            _raise(st)
+        part = k.out.bm, k.out.bn
+    finally:
+        k.busy = False
+    tile_rms_norm.last_partition = part
     return y
 
 
@@ -506,28 +539,33 @@ def tile_rms_norm_matvec(x, nw, W, y, eps=1e-6, *, scale_w=None,
     when not given (workspace=False: no split).  Returns y."""
     if nw.dim() == 1:
         nw = nw.view(1, -1)
-    k = _call
-    a, w, n, out = _in(x), _in(W, 1), _in(nw), _in(y)
-    # the residual's descriptor is the one left without a place in the frame
-    res = None if residual is None else make_in(residual)
-    given = workspace if workspace is not None and workspace is not False \
-        else None
-    h = _stream(stream)
+    k = _take()
+    try:
+        a, w, n, out = _in(x), _in(W, 1), _in(nw), _in(y)
+        # the residual's descriptor is the one left without a place in the
+        # frame
+        res = None if residual is None else make_in(residual)
+        given = workspace if workspace is not None and \
+            workspace is not False else None
+        h = _stream(stream)
 
-    def fill():
-        _fill(k.f, a + w + n + out + (0, 0) +
-              _opts(TG_PREC_NATIVE, checked, None, scale_w, None, given,
-                    write_count, 0 if res is None else ctypes.addressof(res)))
-    fill()
-    if workspace is None:
-        need = lib.tile_rms_norm_matvec_workspace_size(k.a, k.b, k.c)
-        if need:
-            given = torch.empty(need, dtype=torch.uint8, device=y.device)
-            fill()
-    st = lib.tile_rms_norm_matvec(k.a, k.x, float(eps), k.b, k.c, k.o, h)
-    if st:
-        _raise(st)
-    tile_rms_norm_matvec.last_partition = (k.out.bm, k.out.bn)
+        def fill():
+            _fill(k.f, a + w + n + out + (0, 0) +
+                  _opts(TG_PREC_NATIVE, checked, None, scale_w, None, given,
+                        write_count,
+                        0 if res is None else ctypes.addressof(res)))
+        fill()
+        if workspace is None:
+            need = lib.tile_rms_norm_matvec_workspace_size(k.a, k.b, k.c)
+            if need:
+                given = torch.empty(need, dtype=torch.uint8, device=y.device)
+                fill()
+        st = lib.tile_rms_norm_matvec(k.a, k.x, float(eps), k.b, k.c, k.o, h)
+        if st:
+            _raise(st)
+        tile_rms_norm_matvec.last_partition = (k.out.bm, k.out.bn)
+    finally:
+        k.busy = False
     return y
 
 

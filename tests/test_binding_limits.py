@@ -55,3 +55,33 @@ def test_b_trans_is_zero_or_one(b_trans, error):
     for f in (tg.tile_gemm, tg.tile_gemm_noalloc, tg.tile_gemm_plan):
         with pytest.raises(error):
             f(A, B, C, b_trans=b_trans)
+
+
+@pytest.mark.parametrize("call,entry", [
+    (lambda t: tg.tile_gemm(t[0], t[1], t[2], residual=t[2]), "tile_gemm"),
+    (lambda t: tg.tile_add(t[0], t[0], t[3]), "tile_add"),
+    (lambda t: tg.tile_rms_norm(t[0], t[4], t[3]), "tile_rms_norm"),
+    (lambda t: tg.tile_rms_norm_matvec(t[0], t[4], t[5], t[6]),
+     "tile_rms_norm_matvec")])
+def test_a_call_inside_another_leaves_it_alone(monkeypatch, call, entry):
+    """What a signal handler or a finalizer between filling the frame and the
+    library's reading it does: another call of the same thread."""
+    t = [torch.empty(s, dtype=d) for s, d in (
+        ((8, 64), BF), ((64, 32), BF), ((8, 32), torch.float32),
+        ((8, 64), BF), ((64,), BF), ((48, 64), BF), ((8, 48), BF))]
+    other = torch.empty((3, 16), dtype=BF)
+    seen = []
+
+    def library(*args):
+        descs = [a._obj for a in args if hasattr(a, "_obj")]
+        before = [bytes(d) for d in descs]
+        if not seen:
+            seen.append(1)
+            tg.tile_add(other, other, other)
+        assert [bytes(d) for d in descs] == before
+        return 0
+    for e in {entry, "tile_add"}:
+        monkeypatch.setattr(tg.lib, e, library)
+    call(t)
+    assert seen
+    assert not tg._call.held.busy
