@@ -288,6 +288,19 @@ int64_t tiles_of(int64_t M, int64_t N, int s) {
     return ((M + s - 1) / s) * ((N + s - 1) / s);
 }
 
+// Sub-tensor of a configuration that names wavefronts, stages, bk or a
+// schedule but no size: the largest square one that still gives every compute
+// unit close to one.  (Which of those exist depends on the size, so this rule
+// does not move with the defaults below: what it accepts stays accepted.)
+int named_tile(int dt, int64_t M, int64_t N, int cus) {
+    if (cus <= 0) cus = 256;
+    for (int s : {256, 128, 64})
+        if ((dt != TG_F32 || s < 256) &&
+            tiles_of(M, N, s) * 4 >= (int64_t)cus * 3)
+            return s;
+    return 32;
+}
+
 // Default sub-tensor of a tiled product, and LDS stages where they matter
 // (0: the variant table's first).  With t(s) sub-tensors of s x s on `cus`
 // compute units, measured in a graph of one launch each (B stored N x K):
@@ -338,9 +351,7 @@ struct DefaultTile {
 DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, bool b_nk,
                          int cus) {
     if (cus <= 0) cus = 256;
-    const auto t = [&](int s) {
-        return ((M + s - 1) / s) * ((N + s - 1) / s);
-    };
+    const auto t = [&](int s) { return tiles_of(M, N, s); };
     if (dt == TG_F32) {
         const auto rounds = [&](int s) { return (t(s) + cus - 1) / cus; };
         if (t(32) <= 3 * (int64_t)cus && K * 4 >= 4 * 128) return {32, 16, 8};
@@ -638,13 +649,15 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
                         "aligned rows, K (and N for B stored K x N) a "
                         "multiple of 16 bytes, e4m3 B stored N x K");
         if (cfg.bm == 0 && cfg.bn == 0) {
-            const DefaultTile t =
-                default_tile(L.gemm_dt, p.M, p.N, L.Kc, p.b_nk, cus);
-            cfg.bm = cfg.bn = t.size;
             if (cfg.wm == 0 && cfg.wn == 0 && cfg.bk == 0 &&
                 cfg.stages == 0 && cfg.sched == 0) {
+                const DefaultTile t = default_tile(L.gemm_dt, p.M, p.N, L.Kc,
+                                                   p.b_nk, cus);
+                cfg.bm = cfg.bn = t.size;
                 cfg.stages = t.stages;
                 cfg.wm = t.wm;
+            } else {
+                cfg.bm = cfg.bn = named_tile(L.gemm_dt, p.M, p.N, cus);
             }
         } else if (cfg.bm == 0 || cfg.bn == 0) {
             return fail(TG_E_ARG, "config bm/bn: set both or neither");

@@ -1,0 +1,37 @@
+"""Configurations that name wavefronts, stages, bk or a schedule but no size
+take the largest square sub-tensor that gives every compute unit close to one,
+whatever the defaults are, so that they find their kernel (planned for 256
+compute units, without a GPU)."""
+import pytest
+import torch
+
+import paper_2606_15991_amd as tg
+
+BF, F8, F32 = torch.bfloat16, torch.float8_e4m3fn, torch.float32
+
+
+@pytest.mark.parametrize("dt,M,N,K,b_trans,cfg,want", [
+    # narrow outputs whose own default is 64 or 128
+    (BF, 64, 65536, 512, True, dict(sched=3, stages=2), (256, 2, 4, 64, 2)),
+    (BF, 100, 49152, 256, True, dict(bk=32), (256, 2, 4, 32, 4)),
+    (BF, 65536, 64, 512, False, dict(stages=5), (256, 2, 4, 32, 5)),
+    (F8, 17, 51200, 512, True, dict(sched=2), (256, 2, 4, 64, 4)),
+    # an output whose own default is 256
+    (BF, 3072, 3072, 1024, False, dict(wm=2, wn=2, sched=1),
+     (128, 2, 2, 32, 4)),
+    # small ones, whose wavefronts share K by default
+    (BF, 512, 512, 512, True, dict(wm=1, wn=1), (32, 1, 1, 64, 2)),
+    (BF, 1024, 1024, 1024, True, dict(wm=2, wn=2, stages=2),
+     (64, 2, 2, 64, 2)),
+    (F32, 512, 512, 512, True, dict(stages=2), (32, 1, 1, 32, 2)),
+    (F32, 4096, 4096, 512, False, dict(wm=2, wn=2), (128, 2, 2, 32, 2))])
+def test_named_configurations_find_their_kernel(dt, M, N, K, b_trans, cfg,
+                                                want):
+    A = torch.empty((M, K), dtype=dt)
+    B = torch.empty((N, K) if b_trans else (K, N), dtype=dt)
+    C = torch.empty((M, N))
+    got = tg.tile_gemm_plan(A, B, C, b_trans=b_trans, want_map=False,
+                            config={"kind": "tiled", **cfg})[0]
+    assert got["bm"] == got["bn"]
+    assert (got["bm"], got["wm"], got["wn"], got["bk"], got["stages"]) == \
+        want, got
