@@ -158,11 +158,15 @@ typedef struct tg_config {
     int32_t bm, bn, bk;
     int32_t wm, wn;
     int32_t ksplit;       /* skinny kernel: wavefronts sharing one tile's K
-                             (unsplit products of many columns run eight
-                             wavefronts over several tiles instead)        */
+                             (not used where the streaming form runs)       */
     int32_t stages;       /* tiled kernel: LDS stages of the K-tile ring;
                              with TG_SCHED_CROSS, 3 means five slots of one
-                             operand tile each (A or B of a K tile)         */
+                             operand tile each (A or B of a K tile).  Plans
+                             of the skinny kernel: 4 where its streaming
+                             form runs (unsplit products of many columns:
+                             workgroups of eight wavefronts each run
+                             several programs in a row), else 0.  Plans of
+                             the simple kernel: its LDS stages              */
     int32_t sched;        /* tiled kernel: tg_sched                          */
     int32_t splitk;       /* skinny kernel: programs sharing one sub-tensor's
                              K (1..TG_MAX_SPLITK).  With splitk > 1 each

@@ -418,7 +418,6 @@ __global__ __launch_bounds__(256) void skinny_merge_kernel(SkinnyArgs g,
 // 49.5 against 58; bf16 95 against 120 and 89 against 95; (1, 5120, 5120) e4m3
 // 9.6 against 10.3; reading 262 MB alone takes 45 us on this chip.
 constexpr int kStreamWaves = 8;
-constexpr int kStreamRing = 4;
 constexpr int kStreamTile = 16 * 128;                       // bytes
 constexpr int kStreamLds =    // ring, and two sets of partial tiles
     kStreamWaves * (kStreamRing * kStreamTile + 2 * 1024);
@@ -580,16 +579,12 @@ __global__ __launch_bounds__(kStreamWaves * 64) void skinny_stream_kernel(
 // Bytes of LDS of the streaming form, or 0 where it cannot run the product:
 // K of whole 16-byte weight chunks, a block of K for every wavefront, the
 // activations within LDS.
-int64_t stream_lds(int w_dtype, const SkinnyArgs &a) {
-    const int wes = w_dtype == TG_BF16 ? 2 : 1;
-    const int64_t kbytes = (int64_t)a.K * wes;
+int64_t stream_lds(int64_t kbytes, int64_t M, int64_t K, int64_t ldx) {
     const int64_t nkb = (kbytes + 127) / 128;
-    if (a.splitk > 1 || kbytes % 16 || kbytes > 0x7fffffff ||
-        nkb < kStreamWaves)
-        return 0;
-    const int64_t x = ((int64_t)a.K + 127) / 128 * 256 * a.M;
+    if (kbytes % 16 || kbytes > 0x7fffffff || nkb < kStreamWaves) return 0;
+    const int64_t x = (K + 127) / 128 * 256 * M;
     const int64_t lds = kStreamLds + (x + 1023) / 1024 * 1024;
-    return lds <= 160 * 1024 && a.M * a.ldx * 2 < 0x7fffffff ? lds : 0;
+    return lds <= 160 * 1024 && M * ldx * 2 < 0x7fffffff ? lds : 0;
 }
 
 // Whether the streaming form is the faster one.  Its workgroups are dealt
@@ -719,31 +714,35 @@ hipError_t launch_skinny_norm(int w_dtype, int c_bf16, int bn, int ksplit,
     return hipErrorInvalidValue;
 }
 
+int32_t skinny_stream(int w_dtype, int64_t M, int64_t N, int64_t K,
+                      int64_t ldx, int64_t ldw, int32_t bn, int cus) {
+    const int64_t wes = w_dtype == TG_BF16 ? 2 : 1;
+    if (!stream_lds(K * wes, M, K, ldx)) return 0;
+    // one workgroup per compute unit
+    const int64_t progs = (N + bn - 1) / bn;
+    const int64_t groups = cus > 0 ? cus : 256;
+    const int64_t q = (progs + groups - 1) / groups;
+    const int64_t span = (q * bn + 16) * ldw * wes;
+    return span < 0x7fffffff && stream_pays(K * wes, progs, groups, q)
+               ? (int32_t)q : 0;
+}
+
 hipError_t launch_skinny(int w_dtype, int c_bf16, int bn, int ksplit,
-                         const SkinnyArgs &a, int cus, hipStream_t st) {
-    const int64_t lds = bn == a.bn ? stream_lds(w_dtype, a) : 0;
-    if (lds) {
-        // one workgroup per compute unit
+                         const SkinnyArgs &a, int stream, hipStream_t st) {
+    if (stream > 0) {
         const int64_t progs = (a.N + (int64_t)bn - 1) / bn;
-        const int64_t groups = cus > 0 ? cus : 256;
-        const int64_t q = (progs + groups - 1) / groups;
-        const int grid = (int)((progs + q - 1) / q);
-        const int64_t span =
-            (q * bn + 16) * a.ldw * (w_dtype == TG_BF16 ? 2 : 1);
-        if (span < 0x7fffffff &&
-            stream_pays(w_dtype == TG_BF16 ? a.K * (int64_t)2 : a.K, progs,
-                        groups, q)) {
-            if (w_dtype == TG_BF16)
-                return c_bf16
-                           ? launch_stream<TG_BF16, true>(a, (int)q, grid,
-                                                          lds, st)
-                           : launch_stream<TG_BF16, false>(a, (int)q, grid,
-                                                           lds, st);
-            return c_bf16 ? launch_stream<TG_FP8_E4M3, true>(a, (int)q, grid,
-                                                             lds, st)
-                          : launch_stream<TG_FP8_E4M3, false>(a, (int)q,
-                                                              grid, lds, st);
-        }
+        const int grid = (int)((progs + stream - 1) / stream);
+        const size_t lds = (size_t)stream_lds(
+            w_dtype == TG_BF16 ? a.K * (int64_t)2 : a.K, a.M, a.K, a.ldx);
+        if (w_dtype == TG_BF16)
+            return c_bf16
+                       ? launch_stream<TG_BF16, true>(a, stream, grid, lds, st)
+                       : launch_stream<TG_BF16, false>(a, stream, grid, lds,
+                                                       st);
+        return c_bf16
+                   ? launch_stream<TG_FP8_E4M3, true>(a, stream, grid, lds, st)
+                   : launch_stream<TG_FP8_E4M3, false>(a, stream, grid, lds,
+                                                       st);
     }
     if (w_dtype == TG_BF16)
         return launch_bn<TG_BF16>(c_bf16, bn, ksplit, a, st);

@@ -3,7 +3,9 @@
 // The tile schedule below is the single definition of the program ->
 // sub-tensor map: the kernels walk it on the device and tile_gemm_plan
 // exports it on the host, so the map that tile_partition_check validates is
-// the one that runs.
+// the one that runs.  A program is a workgroup, but for the streaming form of
+// the decode product: there a workgroup runs several programs in a row
+// (skinny_stream says how many), each owning what the map gives it.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -165,8 +167,15 @@ struct SkinnyArgs {
     int64_t ldr;
     int32_t res_bf16;
 };
+// Streaming form of an unsplit product: the programs of bn columns that one
+// workgroup runs, one after the other in the order of their columns; 0 where
+// the plain form, a workgroup per program, is the faster or the only one.
+int32_t skinny_stream(int w_dtype, int64_t M, int64_t N, int64_t K,
+                      int64_t ldx, int64_t ldw, int32_t bn, int cus);
+constexpr int kStreamRing = 4;   // tiles of the streaming form's LDS ring
+// stream: skinny_stream's answer (0 with a K split).
 hipError_t launch_skinny(int w_dtype, int c_bf16, int bn, int ksplit,
-                         const SkinnyArgs &a, int cus, hipStream_t st);
+                         const SkinnyArgs &a, int stream, hipStream_t st);
 // Merge of a split decode product: one program per bm x bn sub-tensor of
 // y sums the splitk partial tiles in split order, applies the scales (and
 // the fused normalisation's row scale when norm is set) and stores y.

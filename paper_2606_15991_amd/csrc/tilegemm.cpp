@@ -378,6 +378,8 @@ struct Launch {
     int64_t Kc;        // contraction length seen by the kernel
     int32_t sps;       // decode kernel: K steps per split
     int32_t gm, gn;    // simple kernel: sub-tensors per program
+    bool mixed;        // simple kernel: bf16 x e4m3 on the phased kernel
+    int32_t stream;    // decode kernel: skinny_stream's answer
     Sched s;
 };
 
@@ -455,12 +457,13 @@ void simple_group(Launch &L, const tg_config &cfg, int cus) {
 bool mixed_ok(const Problem &p, const tg_in *A, const tg_in *B,
               const tg_out *C, const Launch &L) {
     const int64_t lim = (int64_t)1 << 31;
+    const int64_t lda = row_stride(*A).ld, ldb = row_stride(*B).ld;
     return p.a_dt == TG_BF16 && p.b_dt == TG_FP8_E4M3 && p.b_nk &&
            L.gm == 2 && L.gn == 2 && L.cfg.bm == 64 && L.cfg.bn == 64 &&
            p.K > 0 && p.K % 16 == 0 && aligned16(A->data) &&
-           aligned16(B->data) && (A->rows == 1 || A->ld % 8 == 0) &&
-           (B->rows == 1 || B->ld % 16 == 0) && A->ld * 2 * 256 < lim &&
-           B->ld * 256 < lim && C->ld * 4 * 256 < lim;
+           aligned16(B->data) && (A->rows == 1 || lda % 8 == 0) &&
+           (B->rows == 1 || ldb % 16 == 0) && lda * 2 * 256 < lim &&
+           ldb * 256 < lim && C->ld * 4 * 256 < lim;
 }
 
 // `have`: workspace bytes the caller supplies; the default K split of a
@@ -514,6 +517,8 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
     }
     int cus = device_cus();
     L.variant = -1;
+    L.mixed = false;
+    L.stream = 0;
     if (cfg.kind == TG_KIND_SKINNY) {
         if (!s_ok)
             return fail(TG_E_UNSUPPORTED,
@@ -633,6 +638,14 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
             cfg.ksplit != 8 && cfg.ksplit != 16)
             return fail(TG_E_UNSUPPORTED, "ksplit %d not in {1,2,4,8,16}",
                         cfg.ksplit);
+        // the streaming form (not of the fused normalisation), reported as
+        // the stages of its ring
+        L.stream = norm || cfg.splitk > 1
+                       ? 0
+                       : skinny_stream(p.b_dt, p.M, p.N, p.K,
+                                       row_stride(*A).ld, row_stride(*B).ld,
+                                       cfg.bn, cus);
+        cfg.stages = L.stream ? kStreamRing : 0;
         cfg.bk = p.b_dt == TG_BF16 ? 32 : 64;
         cfg.wm = 1;
         cfg.wn = 1;
@@ -713,9 +726,6 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
         if (cfg.bm <= 0 || cfg.bn <= 0 || cfg.bm > 64 || cfg.bn > 64)
             return fail(TG_E_UNSUPPORTED,
                         "simple kernel partitions are at most 64 x 64");
-        cfg.bk = 32;
-        cfg.wm = 4;
-        cfg.wn = 1;
         cfg.ksplit = 1;
         if (cfg.splitk > 1)
             return fail(TG_E_UNSUPPORTED, "splitk applies to the decode "
@@ -729,6 +739,14 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
         L.s.n_prog = simple_blocks_m(L) *
                      ((L.s.tiles_n + L.gn - 1) / L.gn);
         L.s.group_m = 1;
+        // K tiles, wavefronts and LDS stages of the kernel that runs
+        L.cfg = cfg;
+        L.mixed = mixed_ok(p, A, B, C, L);
+        cfg.bk = p.a_dt == TG_F32 ? 32 : 64;
+        cfg.wm = L.mixed ? 4 : 2;
+        cfg.wn = !L.mixed && (L.gm * cfg.bm > 64 || L.gn * cfg.bn > 64) ? 4
+                                                                        : 2;
+        cfg.stages = L.mixed ? 4 : 2;
     }
     L.cfg = cfg;
     return TG_OK;
@@ -823,7 +841,7 @@ void features(const Problem &p, const Launch &L, const tg_config &dflt,
     f[10] = lg2((double)c.bm);
     f[11] = lg2((double)c.bn);
     f[12] = lg2(pos(c.wm * c.wn));
-    f[13] = lg2(pos(c.stages));
+    f[13] = c.kind == TG_KIND_TILED ? lg2(pos(c.stages)) : 0.f;
     f[14] = lg2(pos(c.ksplit));
     f[15] = lg2(tiles);
     f[16] = lg2(progs);
@@ -1211,7 +1229,7 @@ tg_status tile_gemm(const tg_in *A, const tg_in *B, tg_out *C,
             a.part = static_cast<float *>(o->workspace);
         }
         e = launch_skinny(p.b_dt, p.c_bf16, L.cfg.bn, L.cfg.ksplit, a,
-                          device_cus(), hs);
+                          L.stream, hs);
         if (e == hipSuccess && a.splitk > 1)
             e = launch_skinny_merge(p.c_bf16, a, false, 0.f, hs);
         return e == hipSuccess ? TG_OK : hip_fail(e, "decode kernel launch");
@@ -1227,8 +1245,7 @@ tg_status tile_gemm(const tg_in *A, const tg_in *B, tg_out *C,
         a.gm = L.gm; a.gn = L.gn;
         a.blocks_m = simple_blocks_m(L);
         a.n_prog = L.s.n_prog;
-        e = mixed_ok(p, A, B, C, L) ? launch_mixed(a, hs)
-                                    : launch_simple(a, hs);
+        e = L.mixed ? launch_mixed(a, hs) : launch_simple(a, hs);
         return e == hipSuccess ? TG_OK : hip_fail(e, "simple kernel launch");
     }
 
