@@ -475,7 +475,9 @@ tg_status tile_error_norm(const void *C, int32_t c_dtype, const double *R,
  * set): every tiled instantiation tile_gemm accepts, and for decode
  * products 16- and 32-column programs plus the width that deals N evenly
  * over whole rounds of the compute units, each with its wavefront counts
- * and K splits.  Writes up to `max` into `out` (host) and returns the total
+ * and K splits.  Configurations that make the same launch (two schedules'
+ * names of one kernel, wavefront counts where the streaming form runs) are
+ * listed once, by the default's name where that is among them.  Writes up to `max` into `out` (host) and returns the total
  * count, or -1 on invalid arguments.  Host only.
  */
 int32_t tile_gemm_candidates(const tg_in *A, const tg_in *B, const tg_out *C,
@@ -491,9 +493,10 @@ typedef struct tg_tune_result {
  * tile_autotune -- run every candidate once (warm-up) then `reps` times on
  * `stream`, timed with HIP events, and record the fastest in the tuning
  * cache.  From four launches on they are dealt over two to four passes over
- * the candidates (a warm-up in each) and the fastest pass's average counts.  C is written (any candidate's result).  results (host, up to
- * max_results entries) and best (host) may be NULL.  Synchronises the
- * stream: not capturable.
+ * the candidates (a warm-up in each) and the fastest pass's average counts.
+ * C is written (any candidate's result).  results (host, up to max_results
+ * entries) and best (host) may be NULL.  Synchronises the stream: not
+ * capturable.
  */
 tg_status tile_autotune(const tg_in *A, const tg_in *B, tg_out *C,
                         const tg_opts *opts, int32_t reps,

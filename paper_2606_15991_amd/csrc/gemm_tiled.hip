@@ -1730,6 +1730,11 @@ static hipError_t prepare_smem(const VariantEntry &e) {
     return err;
 }
 
+const void *tiled_kernel(int variant) {
+    int n;
+    return table(&n)[variant].kernel;
+}
+
 bool tiled_planes(int variant) {
     int n;
     return table(&n)[variant].planes != nullptr;

@@ -136,6 +136,8 @@ const TiledVariant &tiled_variant(int i);
 hipError_t launch_tiled(int variant, const GemmArgs &args, hipStream_t st);
 hipError_t launch_grouped(int variant, int n, int total_tiles, int n_prog,
                           const void *table_dev, hipStream_t st);
+// The variant's kernel: variants of one kernel are names of the same launch.
+const void *tiled_kernel(int variant);
 // Whether variant i also runs products of planes (kp != 0).
 bool tiled_planes(int variant);
 int tiled_occupancy(int variant);  // resident workgroups per CU

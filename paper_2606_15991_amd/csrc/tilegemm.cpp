@@ -760,14 +760,29 @@ host::Key key_of(const Problem &p) {
     return k;
 }
 
-// Every configuration tile_gemm can run for this request.
+tg_config default_config(const Problem &p, const tg_in *A, const tg_in *B,
+                         const tg_out *C);
+
+// Every launch tile_gemm can make for this request, each under one name: the
+// heuristic's where that is one of several (the tuner would choose between
+// names by noise, and the picker learn differences that are none).
 void candidates(const Problem &p, const tg_in *A, const tg_in *B,
                 const tg_out *C, std::vector<tg_config> &out) {
     out.clear();
+    const tg_config dflt = default_config(p, A, B, C);
     auto try_cfg = [&](const tg_config &c) {
         Launch L;
         std::string keep = g_err;
-        if (choose_explicit(p, A, B, C, &c, L, SIZE_MAX) == TG_OK) {
+        tg_status st = choose_explicit(p, A, B, C, &c, L, SIZE_MAX);
+        if (st == TG_OK && L.stream) {
+            // the streaming form has no use for ksplit: the one that the
+            // plain form's rule gives, for calls whose strides need that
+            tg_config one = c;
+            one.ksplit = dflt.kind == TG_KIND_SKINNY && dflt.bn == c.bn &&
+                                 dflt.splitk == 1 ? dflt.ksplit : 0;
+            st = choose_explicit(p, A, B, C, &one, L, SIZE_MAX);
+        }
+        if (st == TG_OK) {
             bool dup = false;
             for (const tg_config &o : out)
                 dup = dup || std::memcmp(&o, &L.cfg, sizeof o) == 0;
@@ -795,10 +810,21 @@ void candidates(const Problem &p, const tg_in *A, const tg_in *B,
                 try_cfg(c);
             }
     const int n = tiled_variant_count();
+    auto is_default = [&](const TiledVariant &v) {
+        return dflt.kind == TG_KIND_TILED && dflt.bm == v.bm &&
+               dflt.bn == v.bn && dflt.bk == v.bk && dflt.wm == v.wm &&
+               dflt.wn == v.wn && dflt.stages == v.stages &&
+               dflt.sched == v.sched;
+    };
     for (int i = 0; i < n; ++i) {
         const TiledVariant &v = tiled_variant(i);
         if (v.dtype != gdt || v.b_nk != (int)p.b_nk || v.c_bf16 != (int)p.c_bf16)
             continue;
+        bool named = false;    // this kernel is listed under another name
+        for (int j = 0; j < n && !is_default(v); ++j)
+            named = named || (j != i && tiled_kernel(j) == tiled_kernel(i) &&
+                              (j < i || is_default(tiled_variant(j))));
+        if (named) continue;
         tg_config c{};
         c.kind = TG_KIND_TILED;
         c.bm = v.bm; c.bn = v.bn; c.wm = v.wm; c.wn = v.wn;

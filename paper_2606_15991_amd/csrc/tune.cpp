@@ -254,6 +254,10 @@ tg_status tile_autotune_grouped(int32_t n, const tg_in *A, const tg_in *B,
         const TiledVariant &v = tiled_variant(i);
         if (v.dtype != TG_BF16 || v.b_nk != b_nk || v.c_bf16 != c_bf16)
             continue;
+        bool named = false;    // an earlier name of the same kernel
+        for (int j = 0; j < i; ++j)
+            named = named || tiled_kernel(j) == tiled_kernel(i);
+        if (named) continue;
         tg_config c{};
         c.kind = TG_KIND_TILED;
         c.bm = v.bm; c.bn = v.bn; c.bk = v.bk; c.wm = v.wm; c.wn = v.wn;

@@ -88,3 +88,37 @@ def test_mixed_tests_run_the_mixed_form(case):
     got = plan(M, N, K, F8, None, (8, 16))
     assert (got["kind"], got["wm"], got["stages"]) == \
         (tg.TG_KIND_SIMPLE, 4, 4), got
+
+
+def launch_of(cfg):
+    """What tells two launches apart: the streaming form has no use for
+    ksplit, the two-stage cross-tile schedules are one kernel."""
+    c = dict(cfg)
+    if c["kind"] == tg.TG_KIND_SKINNY and c["stages"]:
+        c["ksplit"] = 0
+    if c["sched"] == tg.TG_SCHED_CROSS_WARM:
+        c["sched"] = tg.TG_SCHED_CROSS
+    return tuple(sorted(c.items()))
+
+
+@pytest.mark.parametrize("dt,wdt,M,N,K,bns", [
+    (BF, F8, 8, 51200, 5120, {16, 32, 25}), (BF, BF, 1, 5120, 5120, {20}),
+    (BF, F8, 1, 5120, 5120, {20}), (BF, BF, 8192, 8192, 8192, None),
+    (BF, BF, 4096, 4096, 32768, None), (F8, F8, 2048, 2048, 2048, None)])
+def test_candidates_name_each_launch_once(dt, wdt, M, N, K, bns):
+    A = torch.empty((M, K), dtype=dt)
+    B = torch.empty((N, K), dtype=wdt)
+    C = torch.empty((M, N))
+    old = tg.tile_picker_mode(0)
+    try:
+        dflt = tg.tile_gemm_plan(A, B, C, b_trans=True, want_map=False,
+                                 workspace_bytes=1 << 40)[0]
+    finally:
+        tg.tile_picker_mode(old)
+    cands = tg.tile_gemm_candidates(A, B, C, b_trans=True)
+    assert len({launch_of(c) for c in cands}) == len(cands)
+    if bns is None:
+        assert dflt in cands
+    else:
+        assert {c["bn"] for c in cands if c["kind"] == tg.TG_KIND_SKINNY and
+                c["stages"]} >= bns
