@@ -125,7 +125,7 @@ __device__ __forceinline__ void ph_dma2(const i32x4 &srd, uint32_t base,
         : "s"(base), "v"(v[0]), "v"(v[1]), "s"(srd),
           "s"(__builtin_amdgcn_readfirstlane(soff)), "i"(OFF),
           "i"(OFF + 8192)
-        : "memory", "scc");
+        : "memory", "m0", "scc");
 }
 
 // One such load.
@@ -138,7 +138,7 @@ __device__ __forceinline__ void ph_dma1(const i32x4 &srd, uint32_t base,
         :
         : "s"(base), "v"(v), "s"(srd),
           "s"(__builtin_amdgcn_readfirstlane(soff)), "i"(OFF)
-        : "memory", "scc");
+        : "memory", "m0", "scc");
 }
 
 __device__ __forceinline__ int ph_swz(int row) { return (row >> 1) & 7; }

@@ -112,3 +112,20 @@ def test_the_build_refuses_spills():
     for bad in (REMARKS % (0, 0) + REMARKS % (8, 0), REMARKS % (0, 1), ""):
         with pytest.raises(RuntimeError):
             lib_build.check_no_spill("x.hip", bad)
+
+
+def test_inline_assembly_names_what_it_overwrites():
+    """M0 and SCC: the compiler may keep a value of its own in either."""
+    seen = 0
+    for f in sorted(os.listdir(lib_build.CSRC)):
+        text = open(os.path.join(lib_build.CSRC, f)).read()
+        for block in re.findall(r"asm volatile\((.*?)\);", text, re.S):
+            code = " ".join(re.findall(r'"([^"]*)"', block))
+            code = re.sub(r"\\[nt]", " ", code)
+            clobbers = block.rsplit(":", 1)[-1]
+            if re.search(r"\bs_\w+ m0,", code):
+                seen += 1
+                assert '"m0"' in clobbers, (f, block)
+            if re.search(r"\bs_(add|sub|and|or|lshl|cmp)_", code):
+                assert '"scc"' in clobbers, (f, block)
+    assert seen == 7
