@@ -587,16 +587,34 @@ int64_t stream_lds(int64_t kbytes, int64_t M, int64_t K, int64_t ldx) {
     return lds <= 160 * 1024 && M * ldx * 2 < 0x7fffffff ? lds : 0;
 }
 
-// Whether the streaming form is the faster one.  Its workgroups are dealt
-// whole programs, so the last ones may get none: from 85 in 100 workgroups'
-// worth of programs on it is ahead (cold e4m3 weights, one row: (25600, 5120)
-// in 16-column programs, 89 in 100, 28.4 us against 34.9, but (10240, 5120),
-// 83, 18.7 against 17.7 and (12800, 5120), 78, 21.8 against 21.0).  And a row
-// tile ends in a barrier, which needs twelve blocks of K to be hidden: e4m3
-// (4, 51200, 1024), eight, 19.7 us against 16.8, (4, 30000, 1536) 15.5
-// against 16.3.
-bool stream_pays(int64_t kbytes, int64_t progs, int64_t groups, int64_t q) {
-    return kbytes > 11 * 128 && 20 * progs >= 17 * q * groups;
+// Whether the streaming form is the faster one (cold weights, blocks of 128
+// bytes of K).  Its workgroups are dealt whole programs, so the last ones may
+// get none: from 85 in 100 workgroups' worth of programs on it is ahead (e4m3,
+// one row: (25600, 5120) in 16-column programs, 89 in 100, 28.4 us against
+// 34.9, but (10240, 5120), 83, 18.7 against 17.7 and (12800, 5120), 78, 21.8
+// against 21.0).  And a row tile ends in a barrier, which needs K to be
+// hidden:
+//  * twelve blocks: e4m3 (4, 51200, 1024), eight, 19.7 us against 16.8, (4,
+//    30000, 1536), twelve, 15.5 against 16.3;
+//  * more where the plain form has no half-used row tiles and few rows of
+//    activations to load (up to four, programs of up to 16 columns) and the
+//    streaming one several programs a workgroup: bf16 with one or two rows 25
+//    ((1, 51200, 1024), 16 blocks, 21.1 against 19.4, 1536, 24, 29.5 against
+//    27.8, 2048, 32, 1.04 times as fast), with three or four 17 ((4, 16384,
+//    1024), 16, 9.3 against 9.0, 1280, 20, 1.03 times as fast); e4m3 with one or
+//    two rows and up to five programs a workgroup 17 ((1, 16384, 2048), 16,
+//    10.6 against 9.9, 2304, 18, 1.05 times as fast; (1, 23337, 2048) in six
+//    1.05 times).
+bool stream_pays(bool bf16, int64_t M, int64_t kbytes, int64_t bn,
+                 int64_t progs, int64_t groups, int64_t q) {
+    int64_t blocks = 11;
+    if (M <= 4 && bn <= 16 && q > 1) {
+        if (bf16)
+            blocks = M <= 2 ? 24 : 16;
+        else if (M <= 2 && q <= 5)
+            blocks = 16;
+    }
+    return kbytes > blocks * 128 && 20 * progs >= 17 * q * groups;
 }
 
 template <int WDT, bool CBF16>
@@ -723,7 +741,8 @@ int32_t skinny_stream(int w_dtype, int64_t M, int64_t N, int64_t K,
     const int64_t groups = cus > 0 ? cus : 256;
     const int64_t q = (progs + groups - 1) / groups;
     const int64_t span = (q * bn + 16) * ldw * wes;
-    return span < 0x7fffffff && stream_pays(K * wes, progs, groups, q)
+    return span < 0x7fffffff && stream_pays(wes == 2, M, K * wes, bn, progs,
+                                            groups, q)
                ? (int32_t)q : 0;
 }
 

@@ -42,7 +42,14 @@ def decode(bn=0):
 @pytest.mark.parametrize("wdt,M,N,K,bn,stream", [
     # 85 in 100 workgroups' worth of programs: 218 of 256, 435 of 512
     (BF, 8, 217 * 16, 1024, 16, 0), (BF, 8, 218 * 16, 1024, 16, 4),
-    (F8, 2, 435 * 16, 2048, 16, 0), (F8, 2, 436 * 16, 2048, 16, 4),
+    (F8, 2, 435 * 16, 4096, 16, 0), (F8, 2, 436 * 16, 4096, 16, 4),
+    # several programs a workgroup, few rows: 25 blocks of K, 17 with three
+    # or four rows, e4m3 17 with one or two in up to five programs
+    (BF, 2, 16384, 1536, 16, 0), (BF, 2, 16384, 1544, 16, 4),
+    (BF, 3, 16384, 1024, 16, 0), (BF, 4, 16384, 1032, 16, 4),
+    (BF, 2, 16384, 1024, 25, 4), (BF, 5, 16384, 1024, 16, 4),
+    (F8, 2, 20480, 2048, 16, 0), (F8, 2, 20480, 2064, 16, 4),
+    (F8, 2, 23040, 2048, 16, 4), (F8, 3, 20480, 2048, 16, 4),
     # more than eleven blocks of 128 bytes of K
     (BF, 1, 4096, 704, 16, 0), (BF, 1, 4096, 712, 16, 4),
     (F8, 1, 4096, 1408, 16, 0), (F8, 1, 4096, 1424, 16, 4),
