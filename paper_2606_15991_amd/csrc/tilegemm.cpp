@@ -304,12 +304,12 @@ int named_tile(int dt, int64_t M, int64_t N, int cus) {
 // Default sub-tensor of a tiled product, and LDS stages where they matter
 // (0: the variant table's first).  With t(s) sub-tensors of s x s on `cus`
 // compute units, measured in a graph of one launch each (B stored N x K):
-//  256 (phased) where 128 takes more than one program per compute unit and
-//      either t(256) reaches half of them or t(128) passes two: bf16 3072^3
-//      (t(256) = 144) 61 us against 97, 2048 x 5120 x 5120 (160) 96 against
-//      154; but 2816 x 2560 x 3000 (110) 63 against 59, 2048^3 42 against 27.
-//      Not for outputs of at most 128 rows or columns (64 x 65536 x 512: 19
-//      against 15 with 64);
+//  256 (phased) where 128 takes more than two programs per compute unit, as
+//      many as are resident: bf16 3072^3 (t(128) = 576) 61 us against 97, 2048
+//      x 5120 x 5120 (640) 96 against 154; but 4096 x 2048 x 2048 (512) 46
+//      against 42, e4m3 27.6 against 24.2, 2816 x 2560 x 3000 (440) 63 against
+//      59, 2048^3 42 against 27.  Not for outputs of at most 128 rows or
+//      columns (64 x 65536 x 512: 19 against 15 with 64);
 //  128: one round in the phased kernel (B stored N x K): bf16 from a quarter
 //      of the compute units on, 256 x 8192 x 4096 (t(128) = 128) 30.5 us
 //      against 39.4 with 64, 512 x 5120 x 5120 (160) 37.6 against 64.8, 1280^3
@@ -361,8 +361,7 @@ DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, bool b_nk,
     const int64_t nk = K * esize(dt) / 128, side = std::min(M, N);
     if (t(32) <= cus && nk >= 4) return {32, 16, 8};
     if (t(64) <= cus && nk >= 8) return {64, 8, 4};
-    if (side > 128 && t(128) > cus && (2 * t(256) >= cus || t(128) > 2 * cus))
-        return {256, 0};
+    if (side > 128 && t(128) > 2 * cus) return {256, 0};
     if (side > 64 &&
         t(128) * 20 >= (int64_t)cus * (dt == TG_BF16 && b_nk ? 5 : 11))
         return {128, t(128) > cus ? 2 : 0};

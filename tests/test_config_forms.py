@@ -35,3 +35,24 @@ def test_named_configurations_find_their_kernel(dt, M, N, K, b_trans, cfg,
     assert got["bm"] == got["bn"]
     assert (got["bm"], got["wm"], got["wn"], got["bk"], got["stages"]) == \
         want, got
+
+
+@pytest.mark.parametrize("dt,M,N,K,b_trans,size,stages", [
+    (BF, 4096, 2048, 2048, False, 128, 2),     # 512 of 128 x 128: resident
+    (F8, 4096, 2048, 2048, True, 128, 2),
+    (BF, 2300, 3500, 4096, True, 128, 2),      # 504, and 126 of 256 x 256
+    (F8, 4096, 2176, 2048, True, 256, 2),      # 544
+    (BF, 3072, 3072, 512, False, 256, 2)])     # 576
+def test_256_from_more_than_two_programs_of_128(dt, M, N, K, b_trans, size,
+                                                stages):
+    A = torch.empty((M, K), dtype=dt)
+    B = torch.empty((N, K + (-K) % 16 + 16) if b_trans else (K, N), dtype=dt)
+    if b_trans:
+        B = B[:, :K]
+    C = torch.empty((M, N))
+    old = tg.tile_picker_mode(0)
+    try:
+        got = tg.tile_gemm_plan(A, B, C, b_trans=b_trans, want_map=False)[0]
+    finally:
+        tg.tile_picker_mode(old)
+    assert (got["bm"], got["stages"]) == (size, stages), got
