@@ -88,6 +88,36 @@ inline bool simple_shift(uintptr_t base, int64_t ld, int64_t es,
     return ((base | (uint64_t)(ld * es) | (uint64_t)(step * es)) & 3) != 0;
 }
 
+// LDS stages of 128 x 128 sub-tensors where nothing else is named (0: the
+// variant table's first, one program per compute unit).  Past one round of
+// those, programs of two stages, two of them resident per compute unit: bf16
+// 2304^3 (324) 38 us against 42 (K x N 37 against 49), 6000 x 1000 x 512 (376)
+// 15.2 against 18.3 (14.8 against 19.0); e4m3 2304^3 20.4 against 27.5, 4096^3
+// (1024) 69 against 85.  (bf16 stored N x K is up to a tenth ahead in one
+// program at whole rounds of short K: 4096 x 2304 x 256 17.4 against 19.4.)
+inline int rounds_128(int64_t tiles, int cus) {
+    return tiles > (cus > 0 ? cus : 256) ? 2 : 0;
+}
+
+// The same for a grouped launch, whose sub-tensors differ in K: one program
+// per compute unit runs the longest of them faster, two run more of them.
+// `longest` and `sum`: K of the longest sub-tensor and of all together.
+// bf16 by N x K (phased), 12 problems of 2048 x 2048 (3072 sub-tensors): even
+// K 512 90 us against 79 with two stages, 2048 275 against 279, up to twice
+// 2048 366 against 364; 20 of 512 x 512 (320), 2048 ... 4096 (1.26 times the
+// mean at most) 44 against 55, 40 small ones, 256 ... 2560, 27 against 43.
+// K x N: 12 of 2048 x 2048 x 512 103 us against 81, 40 of 512 x 512 (640), 2048
+// ... 6144 (1.51) 141 against 128; but 20 (320) of those 67 against 86.
+inline int grouped_stages_128(int64_t tiles, int64_t longest, int64_t sum,
+                              bool b_nk, int cus) {
+    if (cus <= 0) cus = 256;
+    const bool two = b_nk ? sum <= 1024 * tiles && 4 * longest * tiles <=
+                                                       5 * sum
+                          : tiles > 2 * (int64_t)cus ||
+                                10 * longest * tiles <= 13 * sum;
+    return two ? rounds_128(tiles, cus) : 0;
+}
+
 // Kernel arguments of one tiled product.
 struct GemmArgs {
     const void *a;

@@ -313,14 +313,14 @@ int named_tile(int dt, int64_t M, int64_t N, int cus) {
 //  128: one round in the phased kernel (B stored N x K): bf16 from a quarter
 //      of the compute units on, 256 x 8192 x 4096 (t(128) = 128) 30.5 us
 //      against 39.4 with 64, 512 x 5120 x 5120 (160) 37.6 against 64.8, 1280^3
-//      (100) 13.2 against 15.0;
+//      (100) 13.2 against 15.0 (but with few K tiles behind: 8982 x 112 (71) x
+//      64 4.7 against 4.1, level at x 384);
 //      e4m3, whose 64 reads half the bytes, from eleven in twenty on: 512 x
 //      5120 x 5120 24.4 against 28.9, 1536^3 (144) 10.2 against 10.7, but
 //      1024 x 1536 x 4096 (96) 20.3 against 18.5.  bf16 K x N (eight
 //      wavefronts in step, four stages) from eleven in twenty: 1536^3 18.7
-//      against 22.4, 256 x 8192 x 4096 41.0 against 38.8.  Past one round
-//      two programs of two stages per compute unit: 2304^3 (324) 37.7
-//      against 39.3 in two rounds of the phased kernel;
+//      against 22.4, 256 x 8192 x 4096 41.0 against 38.8.  Past one round two
+//      programs of two stages per compute unit (rounds_128);
 //  64: four stages where all programs are then resident at once (two per
 //      compute unit) and there are at least 36 K tiles: bf16 K x N 256 x 8192
 //      x 4096 38.8 us against 44.6; but 1536^3 (t(64) = 576) 31.5 against
@@ -364,7 +364,7 @@ DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, bool b_nk,
     if (side > 128 && t(128) > 2 * cus) return {256, 0};
     if (side > 64 &&
         t(128) * 20 >= (int64_t)cus * (dt == TG_BF16 && b_nk ? 5 : 11))
-        return {128, t(128) > cus ? 2 : 0};
+        return {128, 0};      // (stages: rounds_128)
     const bool deep = t(64) <= 2 * cus && nk >= 36;
     if (deep || t(64) * 4 >= (int64_t)cus * 3) return {64, deep ? 4 : 2};
     return {32, 0};
@@ -674,6 +674,10 @@ tg_status choose_explicit(const Problem &p, const tg_in *A, const tg_in *B,
         } else if (cfg.bm == 0 || cfg.bn == 0) {
             return fail(TG_E_ARG, "config bm/bn: set both or neither");
         }
+        if (cfg.bm == 128 && cfg.bn == 128 && cfg.wm == 0 && cfg.wn == 0 &&
+            cfg.bk == 0 && cfg.stages == 0 && cfg.sched == 0 &&
+            L.gemm_dt != TG_F32)
+            cfg.stages = rounds_128(tiles_of(p.M, p.N, 128), cus);
         // Long K (at least 16384 and twice the larger of M and N) keeps its
         // own schedule name, which plans and tuning files carry; the kernel
         // is the phased one either way.
@@ -1471,6 +1475,18 @@ tg_status tile_gemm_grouped_prepare(int32_t n, const tg_in *A,
         for (auto &p : ps) work += p.M * p.N;
         cfg.bm = cfg.bn = work >= (int64_t)256 * 256 * 256 ? 256 : 128;
     }
+    const int cus = device_cus();
+    if (cfg.bm == 128 && cfg.bn == 128 && cfg.wm == 0 && cfg.wn == 0 &&
+        cfg.bk == 0 && cfg.stages == 0 && cfg.sched == 0) {
+        int64_t tiles = 0, longest = 0, sum = 0;
+        for (auto &p : ps) {
+            const int64_t t = tiles_of(p.M, p.N, 128);
+            tiles += t;
+            sum += t * p.K;
+            if (t > 0) longest = std::max(longest, p.K);
+        }
+        cfg.stages = grouped_stages_128(tiles, longest, sum, b_nk == 1, cus);
+    }
     bool pp_ok = true, tiles_ok = true, k32_ok = true;
     for (auto &p : ps) {
         pp_ok = pp_ok && chunk_multiple(p.K, TG_BF16);
@@ -1521,7 +1537,6 @@ tg_status tile_gemm_grouped_prepare(int32_t n, const tg_in *A,
     pl.workspace = ws;
     pl.n = n;
     pl.total_tiles = (int32_t)total;
-    int cus = device_cus();
     int occ = cus > 0 ? tiled_occupancy(variant) : 1;
     pl.n_prog = (int32_t)std::min<int64_t>(total,
                                            (int64_t)(cus > 0 ? cus : 256) * occ);

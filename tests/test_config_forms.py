@@ -2,9 +2,14 @@
 take the largest square sub-tensor that gives every compute unit close to one,
 whatever the defaults are, so that they find their kernel (planned for 256
 compute units, without a GPU)."""
+import ctypes
+import os
+import subprocess
+
 import pytest
 import torch
 
+from conftest import ROOT
 import paper_2606_15991_amd as tg
 
 BF, F8, F32 = torch.bfloat16, torch.float8_e4m3fn, torch.float32
@@ -56,3 +61,53 @@ def test_256_from_more_than_two_programs_of_128(dt, M, N, K, b_trans, size,
     finally:
         tg.tile_picker_mode(old)
     assert (got["bm"], got["stages"]) == (size, stages), got
+
+
+@pytest.mark.parametrize("dt,M,N,K,b_trans,stages", [
+    (BF, 2048, 2048, 512, True, 4), (BF, 2048, 2049, 512, True, 2),
+    (BF, 2048, 2048, 512, False, 4), (BF, 2304, 2304, 512, False, 2),
+    (F8, 2048, 2048, 512, True, 4), (F8, 4096, 4096, 512, True, 2),
+    (F32, 4096, 4096, 512, True, 2)])
+def test_partition_of_128_past_one_round(dt, M, N, K, b_trans, stages):
+    """An explicit 128 x 128 partition takes the programs that the default
+    takes of that size: past one round two of two stages per compute unit."""
+    A = torch.empty((M, K), dtype=dt)
+    B = torch.empty((N, K) if b_trans else (K, N), dtype=dt)
+    C = torch.empty((M, N))
+    got = tg.tile_gemm_plan(A, B, C, 128, 128, b_trans=b_trans,
+                            want_map=False)[0]
+    assert got["stages"] == stages, got
+
+
+GROUPED = """
+#include "tg_internal.hpp"
+extern "C" int stages(int64_t tiles, int64_t longest, int64_t sum, int b_nk) {
+    return tg::grouped_stages_128(tiles, longest, sum, b_nk, 256);
+}
+"""
+
+
+def test_grouped_partition_of_128(tmp_path):
+    """The rule of a grouped launch, by (problems, sub-tensors of each, K from,
+    K to): two stages where they were measured ahead of, or level with, one
+    program per compute unit."""
+    src, lib = tmp_path / "g.cpp", tmp_path / "g.so"
+    src.write_text(GROUPED)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC",
+                    "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_2606_15991_amd", "csrc"),
+                    str(src), "-o", str(lib)], check=True)
+    f = ctypes.CDLL(str(lib)).stages
+    f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
+
+    def rule(n, tiles, lo, hi, nk):
+        ks = [lo + (hi - lo) * i // (n - 1) for i in range(n)]
+        return f(n * tiles, max(ks), tiles * sum(ks), nk)
+    for n, tiles, lo, hi, by_nk, by_kn in (
+            (200, 16, 512, 512, 2, 2), (12, 256, 512, 512, 2, 2),
+            (100, 4, 1024, 1024, 2, 2), (12, 256, 2048, 2048, 0, 2),
+            (40, 16, 2048, 2048, 0, 2), (20, 16, 2048, 3450, 0, 2),
+            (20, 16, 2048, 4300, 0, 0), (40, 16, 2048, 6200, 0, 2),
+            (20, 16, 512, 790, 2, 2), (16, 16, 512, 512, 0, 0)):
+        assert rule(n, tiles, lo, hi, 1) == by_nk, (n, tiles, lo, hi)
+        assert rule(n, tiles, lo, hi, 0) == by_kn, (n, tiles, lo, hi)
