@@ -340,8 +340,12 @@ int named_tile(int dt, int64_t M, int64_t N, int cus) {
 //  32  t(32) <= cus: bf16 300 x 300 x 8192 14.4 us against 57 (64, four
 //      stages), 64 x 4096 x 4096 9.4 against 30; e4m3 512^3 (four K tiles)
 //      3.6 against 4.1, but 128^3 (one) 3.2 against 2.9; f32 up to three
-//      rounds: 512^3 5.7 against 14.7, 800^2 x 2048 (t(32) = 625) 37 against
-//      50, but 1024^3 (1024) 28.8 against 26.9;
+//      rounds, from four, eight and sixteen K tiles on: 512^2 x 128 (t(32) =
+//      256) 0.73 of the time of the best other, 640^2 (400) x 192 1.04, x 256
+//      0.89, 800^2 (625) x 384 1.05, x 512 0.97, x 2048 37 us against 50, but
+//      1024^3 (1024) 28.8 against 26.9; 32 rows or columns always from four
+//      on (24576 x 32 x 128 in three rounds 1.4 times 32, which is 1.5 times
+//      what binary32 took in its first form);
 //  64  t(64) <= cus: bf16 1024^3 7.3 us against 10.4, 1024^2 x 4096 15.8
 //      against 30.6 (128), 256 x 2560 x 2560 10.7 against 20.4; e4m3 1024^3
 //      (eight) 5.8 against 6.1, 768^3 (six) 5.2 against 5.1.
@@ -354,8 +358,10 @@ DefaultTile default_tile(int dt, int64_t M, int64_t N, int64_t K, bool b_nk,
     const auto t = [&](int s) { return tiles_of(M, N, s); };
     if (dt == TG_F32) {
         const auto rounds = [&](int s) { return (t(s) + cus - 1) / cus; };
-        if (t(32) <= 3 * (int64_t)cus && K * 4 >= 4 * 128) return {32, 16, 8};
-        if (std::min(M, N) <= 32) return {32, 0};
+        const int64_t side = std::min(M, N), r32 = rounds(32);
+        if (r32 <= 3 && K >= (side <= 32 ? 128 : 64 << r32))
+            return {32, 16, 8};
+        if (side <= 32) return {32, 0};
         return {2 * rounds(64) >= 7 * rounds(128) ? 128 : 64, 0};
     }
     const int64_t nk = K * esize(dt) / 128, side = std::min(M, N);

@@ -111,3 +111,19 @@ def test_grouped_partition_of_128(tmp_path):
             (20, 16, 512, 790, 2, 2), (16, 16, 512, 512, 0, 0)):
         assert rule(n, tiles, lo, hi, 1) == by_nk, (n, tiles, lo, hi)
         assert rule(n, tiles, lo, hi, 0) == by_kn, (n, tiles, lo, hi)
+
+
+@pytest.mark.parametrize("M,N,K,size,wm", [
+    (512, 512, 128, 32, 8), (512, 512, 124, 64, 2),      # one round of 32
+    (640, 640, 256, 32, 8), (640, 640, 252, 64, 2),      # two
+    (800, 800, 512, 32, 8), (800, 800, 508, 64, 2),      # three
+    (103, 6000, 144, 64, 2)])
+def test_binary32_shares_k_where_it_is_long(M, N, K, size, wm):
+    old = tg.tile_picker_mode(0)
+    try:
+        got = tg.tile_gemm_plan(torch.empty((M, K)), torch.empty((N, K)),
+                                torch.empty((M, N)), b_trans=True,
+                                want_map=False)[0]
+    finally:
+        tg.tile_picker_mode(old)
+    assert (got["bm"], got["wm"]) == (size, wm), got
