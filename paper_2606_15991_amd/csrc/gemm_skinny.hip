@@ -604,11 +604,17 @@ int64_t stream_lds(int64_t kbytes, int64_t M, int64_t K, int64_t ldx) {
 //    1024), 16, 9.3 against 9.0, 1280, 20, 1.03 times as fast); e4m3 with one or
 //    two rows and up to five programs a workgroup 17 ((1, 16384, 2048), 16,
 //    10.6 against 9.9, 2304, 18, 1.05 times as fast; (1, 23337, 2048) in six
-//    1.05 times).
-bool stream_pays(bool bf16, int64_t M, int64_t kbytes, int64_t bn,
+//    1.05 times);
+//  * such bf16 products in two programs a workgroup not where workgroups start
+//    a multiple of 256 KiB apart and so read the same channels of memory side
+//    by side: (1, 8192, 4096) 16.4 us against 15.7, (1, 8192, 8192) 31.1
+//    against 29.0, (4, 8192, 8192) 31.5 against 29.8, while K = 5120 is 1.02
+//    and 6144 1.05 times as fast (in four programs, (1, 16384, 4096), 1.05).
+bool stream_pays(bool bf16, int64_t M, int64_t kbytes, int64_t ldw, int64_t bn,
                  int64_t progs, int64_t groups, int64_t q) {
     int64_t blocks = 11;
     if (M <= 4 && bn <= 16 && q > 1) {
+        if (bf16 && q == 2 && q * bn * ldw % (256 * 1024) == 0) return false;
         if (bf16)
             blocks = M <= 2 ? 24 : 16;
         else if (M <= 2 && q <= 5)
@@ -741,8 +747,8 @@ int32_t skinny_stream(int w_dtype, int64_t M, int64_t N, int64_t K,
     const int64_t groups = cus > 0 ? cus : 256;
     const int64_t q = (progs + groups - 1) / groups;
     const int64_t span = (q * bn + 16) * ldw * wes;
-    return span < 0x7fffffff && stream_pays(wes == 2, M, K * wes, bn, progs,
-                                            groups, q)
+    return span < 0x7fffffff && stream_pays(wes == 2, M, K * wes, ldw * wes,
+                                            bn, progs, groups, q)
                ? (int32_t)q : 0;
 }
 

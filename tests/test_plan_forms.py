@@ -50,6 +50,10 @@ def decode(bn=0):
     (BF, 2, 16384, 1024, 25, 4), (BF, 5, 16384, 1024, 16, 4),
     (F8, 2, 20480, 2048, 16, 0), (F8, 2, 20480, 2064, 16, 4),
     (F8, 2, 23040, 2048, 16, 4), (F8, 3, 20480, 2048, 16, 4),
+    # two programs a workgroup, 256 KiB apart (rows padded by eight elements)
+    (BF, 1, 8192, 4088, 16, 0), (BF, 4, 8192, 8184, 16, 0),
+    (BF, 1, 8192, 4096, 16, 4), (BF, 5, 8192, 4088, 32, 4),
+    (BF, 1, 16384, 4088, 16, 4),
     # more than eleven blocks of 128 bytes of K
     (BF, 1, 4096, 704, 16, 0), (BF, 1, 4096, 712, 16, 4),
     (F8, 1, 4096, 1408, 16, 0), (F8, 1, 4096, 1424, 16, 4),
@@ -58,7 +62,8 @@ def decode(bn=0):
     # K of whole 16-byte chunks of the weights
     (F8, 1, 4096, 2040, 16, 0), (F8, 1, 4096, 2048, 16, 4)])
 def test_decode_lines(wdt, M, N, K, bn, stream):
-    got = plan(M, N, K, wdt, decode(bn), (8, 16 - K % 16 if wdt == F8 else 0))
+    got = plan(M, N, K, wdt, decode(bn), (8, 8 if wdt == BF else
+                                          16 - K % 16))
     assert (got["kind"], got["stages"]) == (tg.TG_KIND_SKINNY, stream), got
 
 
