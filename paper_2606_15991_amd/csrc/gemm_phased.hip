@@ -1143,9 +1143,9 @@ hipError_t launch_mixed_out(const SimpleArgs &a, hipStream_t st) {
     typedef Cfg<TG_BF16, 128, 128, 4, 2, true, CBF16, 128, 4,
                 TG_SCHED_LOCKSTEP> C;
     constexpr int lds = Phased128<C, true>::SMEM;
-    static const hipError_t ready = hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&gemm_mixed128_kernel<C>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    static LdsRequest request;
+    const hipError_t ready = request(
+        {reinterpret_cast<const void *>(&gemm_mixed128_kernel<C>)}, lds);
     if (ready != hipSuccess) return ready;
     hipLaunchKernelGGL(gemm_mixed128_kernel<C>, dim3((unsigned)a.n_prog),
                        dim3(C::THREADS), lds, st, a);

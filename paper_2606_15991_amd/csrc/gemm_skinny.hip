@@ -626,9 +626,10 @@ bool stream_pays(bool bf16, int64_t M, int64_t kbytes, int64_t ldw, int64_t bn,
 template <int WDT, bool CBF16>
 hipError_t launch_stream(const SkinnyArgs &a, int q, int grid, size_t lds,
                          hipStream_t st) {
-    static const hipError_t ready = hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&skinny_stream_kernel<WDT, CBF16>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    static LdsRequest request;
+    const hipError_t ready = request(
+        {reinterpret_cast<const void *>(&skinny_stream_kernel<WDT, CBF16>)},
+        160 * 1024);
     if (ready != hipSuccess) return ready;
     hipLaunchKernelGGL((skinny_stream_kernel<WDT, CBF16>), dim3(grid),
                        dim3(kStreamWaves * 64), lds, st, a, q);

@@ -1710,24 +1710,12 @@ const TiledVariant &tiled_variant(int i) {
 }
 
 static hipError_t prepare_smem(const VariantEntry &e) {
-    // LDS beyond the 64 KiB default is requested once per kernel.
-    static std::atomic<int> done[128];
+    static LdsRequest request[128];
     int n;
-    const VariantEntry *base = table(&n);
-    int idx = (int)(&e - base);
-    if (idx >= 0 && idx < 128 && done[idx].load(std::memory_order_acquire))
-        return hipSuccess;
-    hipError_t err = hipFuncSetAttribute(
-        e.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, e.smem);
-    if (err == hipSuccess && e.grouped)
-        err = hipFuncSetAttribute(
-            e.grouped, hipFuncAttributeMaxDynamicSharedMemorySize, e.smem);
-    if (err == hipSuccess && e.planes)
-        err = hipFuncSetAttribute(
-            e.planes, hipFuncAttributeMaxDynamicSharedMemorySize, e.smem);
-    if (err == hipSuccess && idx >= 0 && idx < 128)
-        done[idx].store(1, std::memory_order_release);
-    return err;
+    const int idx = (int)(&e - table(&n));
+    LdsRequest once;
+    return (idx < 128 ? request[idx] : once)({e.kernel, e.grouped, e.planes},
+                                             e.smem);
 }
 
 const void *tiled_kernel(int variant) {

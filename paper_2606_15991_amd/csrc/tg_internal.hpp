@@ -11,9 +11,37 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+#include <initializer_list>
+
 #include "../../include/tilegemm.h"
 
 namespace tg {
+
+// LDS beyond the 64 KiB default, requested once per kernel and device (an
+// attribute of the function on the current device); a request that failed is
+// made again by the next launch.
+class LdsRequest {
+    std::atomic<uint64_t> devices_{0};
+
+public:
+    hipError_t operator()(std::initializer_list<const void *> kernels,
+                          int bytes) {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+        if (devices_.load(std::memory_order_acquire) & bit) return hipSuccess;
+        for (const void *k : kernels) {
+            if (!k) continue;
+            e = hipFuncSetAttribute(
+                k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+            if (e != hipSuccess) return e;
+        }
+        devices_.fetch_or(bit, std::memory_order_release);
+        return hipSuccess;
+    }
+};
 
 // Programs of one launch are dispatched round-robin over the XCDs of the
 // chip (program p lands on XCD p % kXcds).  MI355X has 8.
