@@ -30,7 +30,9 @@ PEAK_TFLOPS = {"bf16": 2516.6, "fp8": 5033.2, "f32": 157.3}
 PEAK_HBM_GBS = 8000.0
 
 
-KERNEL_SOURCES = ["paper_2606_15991_amd/csrc/gemm_tiled.hip",
+KERNEL_SOURCES = ["paper_2606_15991_amd/csrc/gemm_phased.hip",
+                  "paper_2606_15991_amd/csrc/gemm_tiled.hip",
+                  "paper_2606_15991_amd/csrc/tg_tiled.hpp",
                   "paper_2606_15991_amd/csrc/tg_device.hpp",
                   "paper_2606_15991_amd/csrc/tg_internal.hpp"]
 TRAFFIC_PROFILE = "profiles/gemm_tiled_bf16_8192_traffic.md"
