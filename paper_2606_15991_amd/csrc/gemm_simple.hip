@@ -31,10 +31,12 @@
 // load, convert, store, barrier, contract) while programs are few, the
 // matrix cores beyond.  Measured against the element-wise loads and
 // binary32 FMAs from LDS that this kernel replaces: bf16 1111 x 1531 x 1003,
-// 21.7 us against 467; bf16 512 x 5120 x 5120 with e4m3 weights, 49 us
-// (545 TFLOP/s) against 2540.  Three tiles in flight instead of two are no
-// faster (22.6 and 50 us: fewer wavefronts per SIMD), one is slower (62 us
-// with 128 x 128 blocks of four wavefronts).
+// 21.7 us against 467 (432 programs of 64 x 64).  bf16 rows by e4m3 weights:
+// 512 x 5120 x 5120 with B stored K x N 47 us; stored N x K, where K is whole
+// chunks of both, the mixed form of gemm_phased.hip takes it (44 us, 49 here).
+// Three tiles in flight instead of two are no faster (22.6 us and, at those
+// weights, 50: fewer wavefronts per SIMD), one is slower (62 us with 128 x 128
+// blocks of four wavefronts).
 #include "tg_device.hpp"
 #include "tg_internal.hpp"
 

@@ -445,8 +445,12 @@ int32_t simple_blocks_m(const Launch &L) {
 // Sub-tensors per program of the simple kernel: 2 x 2 of the default 64 x 64
 // ones (a 128 x 128 block of eight wavefronts, half the operand traffic per
 // product) where that leaves a program for at least every second compute
-// unit.  Measured: 512 x 5120 x 5120 (160 such programs) 49 us against 53,
-// 1111 x 1531 x 1003 (108) 26 us against 21.7.
+// unit.  Measured, 2 x 2 against 1 x 1: e4m3 weights 512 x 5120 x 5112 (160 such
+// programs) 55 us against 64, stored K x N 47 against 57, bf16 2000 x 2003 x
+// 1003 (256) 27 against 40, 512 x 5120 x 5001 (160) 88 against 103.  Near the
+// line, at 132 programs, bf16 1400 x 1500 x 1003 is behind, 27.8 against 25.0,
+// binary32 x 1001 73 against 58; the mixed form needs the blocks there.  Below
+// it 1111 x 1531 x 1003 (108) ran 26 us in blocks, 21.7 in 432 programs.
 void simple_group(Launch &L, const tg_config &cfg, int cus) {
     L.gm = L.gn = 1;
     if (cfg.bm != 64 || cfg.bn != 64) return;
