@@ -610,9 +610,14 @@ int64_t stream_lds(int64_t kbytes, int64_t M, int64_t K, int64_t ldx) {
 //    by side: (1, 8192, 4096) 16.4 us against 15.7, (1, 8192, 8192) 31.1
 //    against 29.0, (4, 8192, 8192) 31.5 against 29.8, while K = 5120 is 1.02
 //    and 6144 1.05 times as fast (in four programs, (1, 16384, 4096), 1.05).
+//  * bf16 of up to 20 columns a workgroup not past 320 blocks: (1, 5120,
+//    25600), 400 blocks, 51.4 us against 48.4, (1, 5120, 28672) 57.7 against
+//    55.7; 20480 level, 16384 1.01 times as fast, and in 24 columns, (1, 6144,
+//    28672), 1.05.
 bool stream_pays(bool bf16, int64_t M, int64_t kbytes, int64_t ldw, int64_t bn,
                  int64_t progs, int64_t groups, int64_t q) {
     int64_t blocks = 11;
+    if (bf16 && q * bn <= 20 && kbytes > 320 * 128) return false;
     if (M <= 4 && bn <= 16 && q > 1) {
         if (bf16 && q == 2 && q * bn * ldw % (256 * 1024) == 0) return false;
         if (bf16)

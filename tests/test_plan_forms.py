@@ -54,6 +54,9 @@ def decode(bn=0):
     (BF, 1, 8192, 4088, 16, 0), (BF, 4, 8192, 8184, 16, 0),
     (BF, 1, 8192, 4096, 16, 4), (BF, 5, 8192, 4088, 32, 4),
     (BF, 1, 16384, 4088, 16, 4),
+    # up to 20 columns a workgroup: 320 blocks
+    (BF, 1, 5120, 20480, 20, 4), (BF, 1, 5120, 20488, 20, 0),
+    (BF, 1, 5376, 20488, 21, 4), (F8, 1, 5120, 40960, 20, 4),
     # more than eleven blocks of 128 bytes of K
     (BF, 1, 4096, 704, 16, 0), (BF, 1, 4096, 712, 16, 4),
     (F8, 1, 4096, 1408, 16, 0), (F8, 1, 4096, 1424, 16, 4),
