@@ -598,13 +598,17 @@ int64_t stream_lds(int64_t kbytes, int64_t M, int64_t K, int64_t ldx) {
 //    30000, 1536), twelve, 15.5 against 16.3;
 //  * more where the plain form has no half-used row tiles and few rows of
 //    activations to load (up to four, programs of up to 16 columns) and the
-//    streaming one several programs a workgroup: bf16 with one or two rows 25
-//    ((1, 51200, 1024), 16 blocks, 21.1 against 19.4, 1536, 24, 29.5 against
-//    27.8, 2048, 32, 1.04 times as fast), with three or four 17 ((4, 16384,
-//    1024), 16, 9.3 against 9.0, 1280, 20, 1.03 times as fast); e4m3 with one or
-//    two rows and up to five programs a workgroup 17 ((1, 16384, 2048), 16,
-//    10.6 against 9.9, 2304, 18, 1.05 times as fast; (1, 23337, 2048) in six
-//    1.05 times);
+//    streaming one several programs a workgroup.  bf16 with one or two rows:
+//    25 ((1, 51200, 1024), 16 blocks, 21.1 against 19.4, 1536, 24, 29.5 against
+//    27.8, 2048, 32, 1.04 times as fast), only where the blocks go round the
+//    eight wavefronts more than nine tenths evenly ((1, 23008, 2112), 33, 20.4
+//    against 19.1, (1, 20224, 1648), 26, 15.0 against 14.2), and 65 where rows
+//    are no whole 128 bytes, so that every block lies on two lines ((1, 33872,
+//    1808), 29, 28.5 against 23.8, (2, 25856, 2976), 47, 30.9 against 29.2, past
+//    80 level).  bf16 with three or four rows: 17 ((4, 16384, 1024), 16, 9.3
+//    against 9.0, 1280, 20, 1.03 times as fast).  e4m3 with one or two rows and
+//    up to five programs a workgroup: 17 ((1, 16384, 2048), 16, 10.6 against
+//    9.9, 2304, 18, 1.05 times as fast; (1, 23337, 2048) in six 1.05 times);
 //  * such bf16 products in two programs a workgroup not where workgroups start
 //    a multiple of 256 KiB apart and so read the same channels of memory side
 //    by side: (1, 8192, 4096) 16.4 us against 15.7, (1, 8192, 8192) 31.1
@@ -613,15 +617,23 @@ int64_t stream_lds(int64_t kbytes, int64_t M, int64_t K, int64_t ldx) {
 //  * bf16 of up to 20 columns a workgroup not past 320 blocks: (1, 5120,
 //    25600), 400 blocks, 51.4 us against 48.4, (1, 5120, 28672) 57.7 against
 //    55.7; 20480 level, 16384 1.01 times as fast, and in 24 columns, (1, 6144,
-//    28672), 1.05.
+//    28672), 1.05;
+//  * up to four rows not with a second row tile of one or two columns: (1,
+//    4336, 11264) in 17 23.5 us against 21.4, e4m3 (2, 4352, 2816) 6.9 against
+//    6.6, while (1, 5120, 5120) in 20 is level and e4m3 1.07 times as fast.
 bool stream_pays(bool bf16, int64_t M, int64_t kbytes, int64_t ldw, int64_t bn,
                  int64_t progs, int64_t groups, int64_t q) {
     int64_t blocks = 11;
     if (bf16 && q * bn <= 20 && kbytes > 320 * 128) return false;
+    if (M <= 4 && q * bn > 16 && q * bn <= 18) return false;
     if (M <= 4 && bn <= 16 && q > 1) {
         if (bf16 && q == 2 && q * bn * ldw % (256 * 1024) == 0) return false;
+        const int64_t nkb = (kbytes + 127) / 128;
+        const int64_t dealt = (nkb + kStreamWaves - 1) / kStreamWaves *
+                              kStreamWaves;
+        if (bf16 && M <= 2 && 10 * nkb <= 9 * dealt) return false;
         if (bf16)
-            blocks = M <= 2 ? 24 : 16;
+            blocks = M > 2 ? 16 : ldw % 128 ? 64 : 24;
         else if (M <= 2 && q <= 5)
             blocks = 16;
     }

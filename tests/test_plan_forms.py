@@ -45,18 +45,27 @@ def decode(bn=0):
     (F8, 2, 435 * 16, 4096, 16, 0), (F8, 2, 436 * 16, 4096, 16, 4),
     # several programs a workgroup, few rows: 25 blocks of K, 17 with three
     # or four rows, e4m3 17 with one or two in up to five programs
-    (BF, 2, 16384, 1536, 16, 0), (BF, 2, 16384, 1544, 16, 4),
+    # (rows are K + 8 long); 33, 36 and 37 blocks round eight wavefronts
+    (BF, 2, 16384, 1528, 16, 0), (BF, 2, 16384, 1976, 16, 4),
+    (BF, 2, 16384, 2104, 16, 0), (BF, 2, 16384, 2296, 16, 0),
+    (BF, 2, 16384, 2360, 16, 4), (BF, 3, 16384, 2104, 16, 4),
+    # rows of no whole 128 bytes: 65 blocks
+    (BF, 2, 16384, 1984, 16, 0), (BF, 2, 16384, 4096, 16, 0),
+    (BF, 2, 16384, 4160, 16, 4),
     (BF, 3, 16384, 1024, 16, 0), (BF, 4, 16384, 1032, 16, 4),
     (BF, 2, 16384, 1024, 25, 4), (BF, 5, 16384, 1024, 16, 4),
     (F8, 2, 20480, 2048, 16, 0), (F8, 2, 20480, 2064, 16, 4),
     (F8, 2, 23040, 2048, 16, 4), (F8, 3, 20480, 2048, 16, 4),
     # two programs a workgroup, 256 KiB apart (rows padded by eight elements)
     (BF, 1, 8192, 4088, 16, 0), (BF, 4, 8192, 8184, 16, 0),
-    (BF, 1, 8192, 4096, 16, 4), (BF, 5, 8192, 4088, 32, 4),
+    (BF, 1, 8192, 5112, 16, 4), (BF, 5, 8192, 4088, 32, 4),
     (BF, 1, 16384, 4088, 16, 4),
     # up to 20 columns a workgroup: 320 blocks
     (BF, 1, 5120, 20480, 20, 4), (BF, 1, 5120, 20488, 20, 0),
     (BF, 1, 5376, 20488, 21, 4), (F8, 1, 5120, 40960, 20, 4),
+    # a second row tile of one or two columns
+    (BF, 4, 4608, 4096, 18, 0), (BF, 4, 4864, 4096, 19, 4),
+    (BF, 5, 4608, 4096, 18, 4), (BF, 4, 4096, 4096, 16, 4),
     # more than eleven blocks of 128 bytes of K
     (BF, 1, 4096, 704, 16, 0), (BF, 1, 4096, 712, 16, 4),
     (F8, 1, 4096, 1408, 16, 0), (F8, 1, 4096, 1424, 16, 4),
