@@ -21,9 +21,12 @@
 // accumulator update of the 32x32x16 one: matrix instructions alone on
 // random operands run at 2095 TFLOP/s against 1828, with this loop's LDS
 // reads and loads 1530 against 1380, this kernel 763 us against 798.  In
-// cycles, the direct loads: a slot takes 340 cycles against 256 of matrix
-// work, 285 without them (the load path moves 64 bytes a clock and a
-// wavefront waits while it is busy).  Issuing the loads between matrix
+// cycles, the direct loads: a slot takes 340 to 350 cycles against 256 of
+// matrix work (by the counters the matrix cores are busy 76 % of a compute
+// unit's cycles), 285 without them (the load path moves 64 bytes a clock and
+// a wavefront waits while it is busy).  LDS: bf16 2 % of its cycles are bank
+// conflicts, e4m3 49 %, whose lanes read two neighbouring chunks of a row, and
+// transposing reads of a k-major B 26 %; e4m3 is busy 74 % all the same.  Issuing the loads between matrix
 // instructions (832 us), before the reads, staggered over the wavefronts
 // (+-1 %), or with one barrier per two phases (757 us, but e4m3 5 % slower)
 // is no better.

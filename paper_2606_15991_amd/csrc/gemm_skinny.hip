@@ -408,15 +408,16 @@ __global__ __launch_bounds__(256) void skinny_merge_kernel(SkinnyArgs g,
 // of q bn columns in row tiles of 16 whatever bn is.  The wavefronts share
 // K, 128 bytes of every row in turn.  Weights go from memory to LDS by
 // direct loads of whole lines (8 rows of 128 bytes; the 16-byte chunk c of
-// row r at c ^ ((r >> 1) & 7), so that the fragment reads are free of bank
-// conflicts) into a ring of kStreamRing tiles per wavefront, which no other
+// row r at c ^ ((r >> 1) & 7) against bank conflicts, of which 37 % of the
+// LDS cycles are left; wavefronts wait for memory 65 % of their time) into a
+// ring of kStreamRing tiles per wavefront, which no other
 // wavefront reads: no barrier, and the next kStreamRing - 1 tiles in flight
 // throughout, over the end of a row tile too.  The activations stand in LDS
 // once.  At the end of a row tile the
 // wavefronts' partial tiles meet in LDS and are summed in their order.
-// Measured (cold weights): e4m3 (8, 51200, 5120) 55 us against 73, one row
-// 49.5 against 58; bf16 95 against 120 and 89 against 95; (1, 5120, 5120) e4m3
-// 9.6 against 10.3; reading 262 MB alone takes 45 us on this chip.
+// Measured (cold weights): e4m3 (8, 51200, 5120) 53 us against 73, one row
+// 47 against 58; bf16 98 against 118 and 92 against 100; (1, 5120, 5120) e4m3
+// 9.0 against 9.8; reading 262 MB alone takes 45 us on this chip.
 constexpr int kStreamWaves = 8;
 constexpr int kStreamTile = 16 * 128;                       // bytes
 constexpr int kStreamLds =    // ring, and two sets of partial tiles

@@ -133,8 +133,10 @@ __global__ void adam_step(float *__restrict__ p, const float *__restrict__ g,
 // layer by layer (the weight gradients alone 33.1 ms: one thread walked the
 // whole batch per entry), 40 us fused.
 //
-// LDS rows are 68 floats: 16-byte reads along a row and dword reads down a
-// column are both free of bank conflicts.
+// LDS rows are 68 floats, so that neither 16-byte reads along a row nor dword
+// reads down a column fall on few banks; 19 % of the LDS cycles are conflicts
+// all the same.  Wavefronts wait 56 % of their time and the matrix cores are
+// busy 29 % (counters at 20000 x 24, 3 x 64).
 constexpr int kMlpW = 64;            // padded layer width
 constexpr int kMlpLd = 68;           // LDS row stride
 constexpr int kMlpRows = 32;         // batch rows per tile
